@@ -973,15 +973,7 @@ __device__ __forceinline__ cx<T> lane_value(cx<T> v, int src) {
 // In a wave-private tile lane b of a pencil holds e = b + q L/4 (q = 0..3); the elements
 // e > L/2 are conj(A_{L-e}), and L - e is an element that lane (L/4 - b) mod L/4 of the same
 // pencil loads for q = 0 or 1, so they come by cross-lane permutes instead of second loads.
-// Paired x tiles (k_x2p): two waves share each row pair, so the pencil slot p of a wave-private
-// tile (ppw = 256 / L slots per wave) maps to row pair (p / (2 ppw)) ppw + p % ppw of the block.
-template <int L>
-__device__ __forceinline__ int paired_pair(int p) {
-    constexpr int ppw = 256 / L;
-    return (p / (2 * ppw)) * ppw + p % ppw;
-}
-
-template <typename T, int L, class F, bool PAIRED = false>
+template <typename T, int L, class F>
 __device__ __forceinline__ void load_row_pairs(const cx<T> *in, long long pair0, int Pact, long long rows, cx<T> *c) {
     constexpr int KX = L / 2 + 1;
     if constexpr (F::WP) {
@@ -989,7 +981,6 @@ __device__ __forceinline__ void load_row_pairs(const cx<T> *in, long long pair0,
         static_assert(F::template nin<1>() == 4, "one radix-4 butterfly per thread");
         int p, b;
         F::template in_pos<1>(0, p, b);
-        if constexpr (PAIRED) p = paired_pair<L>(p);
         const bool ok = p < Pact;
         const long long r0 = 2 * (pair0 + p);
         const bool okb = ok && r0 + 1 < rows;
@@ -1025,7 +1016,6 @@ __device__ __forceinline__ void load_row_pairs(const cx<T> *in, long long pair0,
         c[2] = mk<T>(A2.x - B2.y, A2.y + B2.x);
         c[3] = mk<T>(A3.x - B3.y, A3.y + B3.x);
     } else {
-        static_assert(!PAIRED, "paired tiles are wave-private");
 #pragma unroll
         for (int i = 0; i < F::template nin<1>(); ++i) {
             int p, e;
@@ -1047,26 +1037,19 @@ __device__ __forceinline__ void load_row_pairs(const cx<T> *in, long long pair0,
 // (C held in split): A_k = (C_k + conj C_{L-k}) / 2, B_k = (C_k - conj C_{L-k}) / (2i).  In a
 // wave-private tile each wave splits its own pencils (lanes along k); otherwise the block does
 // (split must have been synchronized accordingly by the caller).
-// With dkx > 0 both half spectra are multiplied by i k_x (k_x = k dkx, zero on the Nyquist column).
-template <typename T, int L, class F, bool PAIRED = false>
-__device__ __forceinline__ void split_rows(const cx<T> *split, cx<T> *out, long long pair0, int Pact, long long rows,
-                                           T dkx = T(0)) {
+template <typename T, int L, class F>
+__device__ __forceinline__ void split_rows(const cx<T> *split, cx<T> *out, long long pair0, int Pact, long long rows) {
     constexpr int KX = L / 2 + 1;
     auto coeffs = [&](int p, int k, cx<T> &A, cx<T> &B) {
         const cx<T> ck = split[F::lidx(p, k)];
         const cx<T> cm = split[F::lidx(p, k == 0 ? 0 : L - k)];
         A = mk<T>(T(0.5) * (ck.x + cm.x), T(0.5) * (ck.y - cm.y));
         B = mk<T>(T(0.5) * (ck.y + cm.y), T(-0.5) * (ck.x - cm.x));
-        if (dkx > T(0)) {
-            const T kx = (L % 2 == 0 && 2 * k == L) ? T(0) : T(k) * dkx;
-            A = mk<T>(-kx * A.y, kx * A.x);
-            B = mk<T>(-kx * B.y, kx * B.x);
-        }
     };
-    auto one = [&](int p, int pr, int k) {
+    auto one = [&](int p, int k) {
         cx<T> A, B;
         coeffs(p, k, A, B);
-        const long long r0 = 2 * (pair0 + pr);
+        const long long r0 = 2 * (pair0 + p);
         ct::gst(out + r0 * KX + k, A);
         if (r0 + 1 < rows) ct::gst(out + (r0 + 1) * KX + k, B);
     };
@@ -1076,372 +1059,22 @@ __device__ __forceinline__ void split_rows(const cx<T> *split, cx<T> *out, long 
         constexpr int nb = L / 4;
         const int lane = (int)threadIdx.x % 64;
         const int p = ((int)threadIdx.x / 64) * (64 / nb) + lane / nb;
-        const int pr = PAIRED ? paired_pair<L>(p) : p;
         const int b = lane % nb;
-        if (pr < Pact) {
-            one(p, pr, b);
-            one(p, pr, b + nb);
+        if (p < Pact) {
+            one(p, b);
+            one(p, b + nb);
             if (b < 2) {
                 cx<T> A, B;
                 coeffs(p, 2 * nb, A, B);
-                const long long r = 2 * (pair0 + pr) + b;
+                const long long r = 2 * (pair0 + p) + b;
                 if (r < rows) ct::gst(out + r * KX + 2 * nb, b == 0 ? A : B);
             }
         }
     } else {
-        static_assert(!PAIRED, "paired tiles are wave-private");
         for (int j = threadIdx.x; j < Pact * KX; j += (int)blockDim.x) {
             const int p = j / KX;
-            one(p, p, j - p * KX);
+            one(p, j - p * KX);
         }
-    }
-}
-
-// Nodewise variants of X2: FP64 eq. (Phi); FP32 differences from the reference (eq. (Phi),
-// x2_node_diff); FP64 with an alternative functional chosen by X2Args::hs.
-enum X2Node { X2N_FP64 = 0, X2N_D32 = 1, X2N_ALT = 2 };
-
-// X2: ten weighted-density spectra after the y inverse -> inverse x -> pointwise dPhi/dn
-// (eq. Phi) -> forward x -> half spectra, in place in specB.  Register budget of two waves per
-// SIMD: the FP64 kernel would otherwise take one (344 registers; a few spills are cheaper).
-template <typename T, int L, int NODE = X2N_FP64>
-__global__ __launch_bounds__(XTile<L>::NTB) __attribute__((amdgpu_waves_per_eu(2))) void
-k_x2c(Geo g_in, X2Args a) {
-    using XT = XTile<L>;
-    constexpr int PB = XT::PB, NTB = XT::NTB, KX = XT::KX;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PB, NTB, true, 2, XT::PAD>;
-    constexpr int NO = F::template nout<1>();
-    static_assert(NO == F::template nin<-1>(), "forward must start where the inverse ends");
-    const int prob = (int)blockIdx.z;
-    if (prob > 0) {
-        const long long o = (long long)prob * g_in.pstride;
-        g_in = shift(g_in, o);
-        a = shift(a, o);
-    }
-    const Geo &g = g_in;
-    if (gated_off(a.gate)) return;
-    const T dk0 = T(g.cs->dk[0]);   // k_x step, read before any store
-    __shared__ cx<T> lds[F::LDS_ELEMS + F::TILE];
-    cx<T> *split = lds + F::LDS_ELEMS;
-    const long long N = g.N, NC = g.NC;
-    const long long rows = (long long)g.ny * g.nz;
-    const long long npairs = (rows + 1) / 2;
-    const long long pair0 = (long long)blockIdx.x * PB;
-    const int Pact = (int)min((long long)PB, npairs - pair0);
-    const cx<T> *tw = twp<T>(g, 0);
-    // wave-private tiles: the twiddles of all 20 transforms, once, in registers
-    typename F::Twiddles trw;
-    if constexpr (F::WP) F::load_twiddles(trw, tw);
-    const bool n3only = a.mode == X2_N3_ONLY;
-    const int nf = n3only ? 1 : DFT_NALPHA;
-    // X2N_D32 (FP32 differences from the reference, no FP64 copies asked for): the nodewise
-    // difference in FP32 (x2_node_diff); the launcher picks it.
-    constexpr bool D32 = NODE == X2N_D32;
-    static_assert(!D32 || std::is_same<T, float>::value, "FP32 difference path");
-    cx<T> vals[DFT_NALPHA][NO];
-    cx<T> v[F::V];
-    int ph = 0;
-    // all loads first (every field's inputs in flight together), then the transforms
-    static_assert(NO == F::template nin<1>(), "inputs and outputs share registers");
-#pragma unroll
-    for (int f = 0; f < DFT_NALPHA; ++f) {
-        if (f >= nf) continue;
-        if (f == 7 && g.compact) {
-            // compact layout: n_V2,x = -i k_x n3 (k_x zero on the Nyquist column), formed here
-            const T dkx = T(g.cs->dk[0]);
-#pragma unroll
-            for (int i = 0; i < NO; ++i) {
-                int p, e;
-                F::template in_pos<1>(i, p, e);
-                const T kx = (L % 2 == 0 && 2 * e == L) ? T(0) : T(e <= L / 2 ? e : e - L) * dkx;
-                vals[7][i] = mk<T>(kx * vals[3][i].y, -kx * vals[3][i].x);
-            }
-            continue;
-        }
-        load_row_pairs<T, L, F>(reinterpret_cast<const cx<T> *>(a.specB) + (long long)f * NC, pair0, Pact, rows,
-                                vals[f]);
-    }
-    // D32: the reference weighted densities of a register's two nodes, fetched one register
-    // ahead of the nodewise work (the first before the transforms) so their latency is hidden
-    constexpr int NRB = D32 ? 2 : 1;
-    float nrc[NRB][2][DFT_NALPHA];
-    auto fetch_nref = [&](int i, float (&dst)[2][DFT_NALPHA]) {
-        int p, e;
-        const bool ok = F::template out_pos<1>(i, p, e) && p < Pact;
-        const long long r0 = 2 * (pair0 + p);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const bool okh = ok && r0 + h < rows;
-            const long long idx = (r0 + h) * L + e;
-#pragma unroll
-            for (int f = 0; f < DFT_NALPHA; ++f) dst[h][f] = okh ? ct::cld(a.nref + f * N + idx) : 0.0f;
-        }
-    };
-    if constexpr (D32) fetch_nref(0, nrc[0]);
-#pragma unroll
-    for (int f = 0; f < DFT_NALPHA; ++f) {
-        if (f >= nf) continue;
-#pragma unroll
-        for (int i = 0; i < NO; ++i) v[i] = vals[f][i];
-        if constexpr (F::WP) F::template run<1>(v, lds, ph, trw);
-        else F::template run<1>(v, lds, ph, tw);
-#pragma unroll
-        for (int i = 0; i < NO; ++i) vals[f][i] = v[i];
-    }
-    double mloc = -INFINITY;
-    int flag = 0;
-#pragma unroll
-    for (int i = 0; i < NO; ++i) {
-        if constexpr (D32) {
-            if (i + 1 < NO) fetch_nref(i + 1, nrc[(i + 1) % NRB]);
-        }
-        int p, e;
-        if (!(F::template out_pos<1>(i, p, e) && p < Pact)) continue;
-        const long long r0 = 2 * (pair0 + p);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const long long r = r0 + h;
-            if (r >= rows) break;
-            const long long idx = r * L + e;
-            if (n3only) {
-                double n3 = h == 0 ? (double)vals[0][i].x : (double)vals[0][i].y;
-                if (a.nref) n3 += (double)a.nref[3 * N + idx];
-                if (!isfinite(n3)) flag |= 5;   // 1: evaluation non-finite, 4: n3 non-finite
-                mloc = fmax(mloc, n3);
-                continue;
-            }
-            if constexpr (D32) {
-                float dn[DFT_NALPHA], dd[DFT_NALPHA];
-#pragma unroll
-                for (int f = 0; f < DFT_NALPHA; ++f) dn[f] = h == 0 ? vals[f][i].x : vals[f][i].y;
-                x2_node_diff(nrc[i % NRB][h], dn, dd, mloc, flag);
-#pragma unroll
-                for (int f = 0; f < DFT_NALPHA; ++f) {
-                    if (h == 0) vals[f][i].x = dd[f];
-                    else vals[f][i].y = dd[f];
-                }
-            } else {
-                double n[DFT_NALPHA], d[DFT_NALPHA];
-#pragma unroll
-                for (int f = 0; f < DFT_NALPHA; ++f) n[f] = h == 0 ? (double)vals[f][i].x : (double)vals[f][i].y;
-                x2_node<NODE == X2N_ALT>(a, N, idx, n, d, mloc, flag);
-#pragma unroll
-                for (int f = 0; f < DFT_NALPHA; ++f) {
-                    if (h == 0) vals[f][i].x = T(d[f]);
-                    else vals[f][i].y = T(d[f]);
-                }
-            }
-        }
-        if (!n3only && r0 + 1 >= rows) {
-            // the missing partner row transforms as zero
-#pragma unroll
-            for (int f = 0; f < DFT_NALPHA; ++f) vals[f][i].y = T(0);
-        }
-    }
-    if (flag & 4) mloc = INFINITY;   // the n3 bound needs finite n3 only
-    block_reduce_nt<true, NTB>(mloc, flag, a.red.mpart + blockIdx.x, a.red.mflag + blockIdx.x);
-    if (n3only) return;
-#pragma unroll
-    for (int f = 0; f < DFT_NALPHA; ++f) {
-#pragma unroll
-        for (int i = 0; i < NO; ++i) v[i] = vals[f][i];
-        if constexpr (F::WP) F::template run<-1>(v, lds, ph, trw);
-        else F::template run<-1>(v, lds, ph, tw);
-#pragma unroll
-        for (int i = 0; i < F::template nout<-1>(); ++i) {
-            int p, e;
-            if (F::template out_pos<-1>(i, p, e)) split[F::lidx(p, e)] = v[i];
-        }
-        F::sync();
-        // compact layout: the x components of the vector derivatives leave multiplied by i k_x
-        const T dkx = (g.compact && (f == 4 || f == 7)) ? dk0 : T(0);
-        split_rows<T, L, F>(split, reinterpret_cast<cx<T> *>(a.specB) + (long long)f * NC, pair0, Pact, rows, dkx);
-    }
-}
-
-// X2 on wave-private tiles with the ten fields of every row pair shared by two waves of the
-// block.  Wave h of a pair transforms five fields, x2_half_field(h, 0..4) (h = 0: n0..n3 and
-// nV2,x, so the compact layout forms nV2,x = -i k_x n3 in the same wave; h = 1: the nV1
-// components and nV2,y, nV2,z), and does the nodewise work at the nodes of its registers
-// q = 2h, 2h + 1; the other five values of those nodes come from the partner wave through LDS,
-// and their derivatives go back the same way.  Half the fields per wave halves the registers the
-// transforms hold (FP32: three waves fit per SIMD where k_x2c fits two; FP64: two without the
-// spills of k_x2c), for the same arithmetic in the same order.  Nodewise work: FP32, the
-// difference from the reference (x2_node_diff, FP32-mixed evaluations); FP64, x2_node with
-// eq. (Phi), every mode but the n3-only one.
-template <typename T, int L>
-struct XPairTile {
-    static constexpr int PF = 1024 / L;   // pencil slots of a block (four waves)
-    static constexpr int NTB = 256;
-    static constexpr int PB = PF / 2;     // row pairs of a block
-    static constexpr int WPE = sizeof(T) == 4 ? 3 : 2;   // waves per SIMD the registers allow
-};
-
-__host__ __device__ constexpr int x2_half_field(int h, int j) {
-    return h == 0 ? (j < 4 ? j : 7) : (j < 3 ? 4 + j : 5 + j);
-}
-
-// Exchange slot s (0..639: field j, register k, lane as (2 j + k) 64 + lane) of wave w in the
-// wave's own LDS regions of the transform tile: pencils w 256/L.. of the two transform buffers
-// and of the split buffer, 256 elements each (whole pencils of a wave-private tile).
-template <class F, typename T>
-__device__ __forceinline__ cx<T> *x2p_slot(cx<T> *lds, int w, int s) {
-    static_assert(F::TILE == 1024 && F::LDS_ELEMS == 2 * F::TILE, "four waves of 256 elements per buffer");
-    return lds + (s >> 8) * F::TILE + w * 256 + (s & 255);
-}
-
-// Nodewise work of one paired wave (H: its half) with the swap through LDS: the own fields at the
-// partner's registers go out to the own slots; after a barrier the wave takes the partner's fields
-// at its own registers q = 2H + k from the partner's slots, one register at a time, and leaves the
-// partner's derivatives in the same place; after a second barrier it reads its own derivatives at
-// the partner's registers back.  Between the barriers only the partner touches a wave's slots;
-// outside them the slots are the wave's own transform regions.  Every wave of the block passes
-// both barriers.
-template <typename T, int L, class F, int H>
-__device__ __forceinline__ void x2p_swap_and_nodes(const X2Args &a, long long N, long long pair0, int Pact,
-                                                   long long rows, cx<T> *lds, int wave, int lane,
-                                                   cx<T> (&vals)[5][4], double &mloc, int &flag) {
-    constexpr int QP = 2 * (1 - H);   // the partner's registers
-    F::sync();   // the forward transforms' reads of the same regions precede the writes below
-#pragma unroll
-    for (int j = 0; j < 5; ++j)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) *x2p_slot<F>(lds, wave, (2 * j + k) * 64 + lane) = vals[j][QP + k];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int i = 2 * H + k;
-        int p, e;
-        F::template out_pos<1>(i, p, e);
-        const int pr = paired_pair<L>(p);
-        const long long r0 = 2 * (pair0 + pr);
-        cx<T> oth[5];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) oth[j] = *x2p_slot<F>(lds, wave ^ 1, (2 * j + k) * 64 + lane);
-#pragma unroll
-        for (int hr = 0; hr < 2; ++hr) {
-            const bool ok = pr < Pact && r0 + hr < rows;
-            const long long idx = (r0 + hr) * L + e;
-            T dn[DFT_NALPHA], dd[DFT_NALPHA];
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                dn[x2_half_field(H, j)] = hr == 0 ? vals[j][i].x : vals[j][i].y;
-                dn[x2_half_field(1 - H, j)] = hr == 0 ? oth[j].x : oth[j].y;
-            }
-            if (ok) {
-                if constexpr (sizeof(T) == 4) {
-                    float nr[DFT_NALPHA];
-#pragma unroll
-                    for (int f = 0; f < DFT_NALPHA; ++f) nr[f] = ct::cld(a.nref + f * N + idx);
-                    x2_node_diff(nr, dn, dd, mloc, flag);
-                } else {
-                    x2_node<false>(a, N, idx, dn, dd, mloc, flag);
-                }
-            } else {
-#pragma unroll
-                for (int f = 0; f < DFT_NALPHA; ++f) dd[f] = T(0);   // pairs past Pact, the missing partner row
-            }
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                if (hr == 0) {
-                    vals[j][i].x = dd[x2_half_field(H, j)];
-                    oth[j].x = dd[x2_half_field(1 - H, j)];
-                } else {
-                    vals[j][i].y = dd[x2_half_field(H, j)];
-                    oth[j].y = dd[x2_half_field(1 - H, j)];
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 5; ++j) *x2p_slot<F>(lds, wave ^ 1, (2 * j + k) * 64 + lane) = oth[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 5; ++j)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) vals[j][QP + k] = *x2p_slot<F>(lds, wave, (2 * j + k) * 64 + lane);
-    F::sync();   // the reads above precede the inverse transforms' writes to the same regions
-}
-
-template <typename T, int L>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XPairTile<T, L>::WPE))) void
-k_x2p(Geo g_in, X2Args a) {
-    using XP = XPairTile<T, L>;
-    constexpr int PF = XP::PF, NTB = XP::NTB, PB = XP::PB;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PF, NTB, true, 2, 0>;
-    static_assert(F::WP, "paired tiles are wave-private");
-    static_assert(NTB == 256, "the launch bound above");
-    static_assert(F::template nout<1>() == 4 && F::template nin<-1>() == 4, "one radix-4 butterfly per thread");
-    const int prob = (int)blockIdx.z;
-    if (prob > 0) {
-        const long long o = (long long)prob * g_in.pstride;
-        g_in = shift(g_in, o);
-        a = shift(a, o);
-    }
-    const Geo &g = g_in;
-    if (gated_off(a.gate)) return;
-    const T dk0 = T(g.cs->dk[0]);   // k_x step, read before any store
-    __shared__ cx<T> lds[F::LDS_ELEMS + F::TILE];
-    cx<T> *split = lds + F::LDS_ELEMS;
-    const long long N = g.N, NC = g.NC;
-    const long long rows = (long long)g.ny * g.nz;
-    const long long npairs = (rows + 1) / 2;
-    const long long pair0 = (long long)blockIdx.x * PB;
-    const int Pact = (int)min((long long)PB, npairs - pair0);
-    const cx<T> *tw = twp<T>(g, 0);
-    typename F::Twiddles trw;
-    F::load_twiddles(trw, tw);
-    const int wave = (int)threadIdx.x / 64, lane = (int)threadIdx.x % 64, h = wave & 1;
-    cx<T> vals[5][4];
-    cx<T> v[F::V];
-    int ph = 0;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        const int f = x2_half_field(h, j);
-        if (f == 7 && g.compact) {
-            // compact layout: n_V2,x = -i k_x n3 (k_x zero on the Nyquist column), from field 3 (j = 3)
-            const T dkx = T(g.cs->dk[0]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int p, e;
-                F::template in_pos<1>(i, p, e);
-                const T kx = (L % 2 == 0 && 2 * e == L) ? T(0) : T(e <= L / 2 ? e : e - L) * dkx;
-                vals[j][i] = mk<T>(kx * vals[3][i].y, -kx * vals[3][i].x);
-            }
-            continue;
-        }
-        load_row_pairs<T, L, F, true>(reinterpret_cast<const cx<T> *>(a.specB) + (long long)f * NC, pair0, Pact, rows,
-                                      vals[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = vals[j][i];
-        F::template run<1>(v, lds, ph, trw);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) vals[j][i] = v[i];
-    }
-    double mloc = -INFINITY;
-    int flag = 0;
-    // the halves take constant register indices (a run-time choice would put vals in scratch)
-    if (h == 0) x2p_swap_and_nodes<T, L, F, 0>(a, N, pair0, Pact, rows, lds, wave, lane, vals, mloc, flag);
-    else x2p_swap_and_nodes<T, L, F, 1>(a, N, pair0, Pact, rows, lds, wave, lane, vals, mloc, flag);
-    if (flag & 4) mloc = INFINITY;   // the n3 bound needs finite n3 only
-    block_reduce_nt<true, NTB>(mloc, flag, a.red.mpart + blockIdx.x, a.red.mflag + blockIdx.x);
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = vals[j][i];
-        F::template run<-1>(v, lds, ph, trw);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int p, e;
-            if (F::template out_pos<-1>(i, p, e)) split[F::lidx(p, e)] = v[i];
-        }
-        F::sync();
-        const int f = x2_half_field(h, j);
-        const T dkx = (g.compact && (f == 4 || f == 7)) ? dk0 : T(0);
-        split_rows<T, L, F, true>(split, reinterpret_cast<cx<T> *>(a.specB) + (long long)f * NC, pair0, Pact, rows, dkx);
     }
 }
 
@@ -1451,7 +1084,7 @@ k_x2p(Geo g_in, X2Args a) {
 template <typename T, int L>
 __global__ __launch_bounds__(XTile<L>::NTB) void k_x1c(Geo g_in, XFwdArgs a) {
     using XT = XTile<L>;
-    constexpr int PB = XT::PB, NTB = XT::NTB, KX = XT::KX;
+    constexpr int PB = XT::PB, NTB = XT::NTB;
     using F = ct::Fft<T, typename ct::XPlan<L>::type, PB, NTB, true, 2, XT::PAD>;
     const int prob = (int)blockIdx.z;
     if (prob > 0) {
@@ -1520,7 +1153,7 @@ __global__ __launch_bounds__(XTile<L>::NTB) void k_x1c(Geo g_in, XFwdArgs a) {
 template <typename T, int L>
 __global__ __launch_bounds__(XTile<L>::NTB) void k_x3c(Geo g_in, X3Args a) {
     using XT = XTile<L>;
-    constexpr int PB = XT::PB, NTB = XT::NTB, KX = XT::KX;
+    constexpr int PB = XT::PB, NTB = XT::NTB;
     using F = ct::Fft<T, typename ct::XPlan<L>::type, PB, NTB, true, 2, XT::PAD>;
     const int prob = (int)blockIdx.z;
     if (prob > 0) {

@@ -1,31 +1,31 @@
 // Launchers of the compiled-length X2 pass for the alternative hard-sphere functionals
 // (Rosenfeld's original vector form, White Bear): FP64 nodewise work in kernels of their own,
 // so the kernels of eq. (Phi) keep their register budget.
-#include "ct_kernels.h"
+#include "ct_x2.h"
 
 namespace dft {
 
 template <typename T, int L>
-static void launch_x2c_alt_len(const Geo &g, const X2Args &a, hipStream_t s) {
-    const long long npairs = ((long long)g.ny * g.nz + 1) / 2;
-    const long long nb = ct_cdiv(npairs, XTile<L>::PB);
-    if (nb > a.red.cap) throw std::runtime_error("x2: reduction buffer too small");
-    const dim3 grid((unsigned)nb, 1, (unsigned)g.nprob);
-    hipLaunchKernelGGL((k_x2c<T, L, X2N_ALT>), grid, dim3(XTile<L>::NTB), 0, s, g, a);
-    ct_check("x2 (compiled length, alternative functional)");
+static int launch_x2_alt_len(const Geo &g, const X2Args &a, hipStream_t s) {
+    if constexpr (std::is_same<T, double>::value) {
+        if (a.mode == X2_HESS) return launch_x2_form<T, L, X2N_HESS_ALT>(g, a, s);
+    } else if (a.mode == X2_HESS) {
+        throw std::runtime_error("x2: the Hessian mode has FP64 transforms");
+    }
+    return launch_x2_form<T, L, X2N_ALT>(g, a, s);
 }
 
 template <typename T>
-bool launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s) {
+int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s) {
     switch (g.nx) {
-#define DFT_CASE(n) case n: launch_x2c_alt_len<T, n>(g, a, s); return true;
+#define DFT_CASE(n) case n: return launch_x2_alt_len<T, n>(g, a, s);
         DFT_CT_LENGTHS(DFT_CASE)
 #undef DFT_CASE
-        default: return false;
+        default: return 0;
     }
 }
 
-template bool launch_x2_alt_ct<double>(const Geo &, const X2Args &, hipStream_t);
-template bool launch_x2_alt_ct<float>(const Geo &, const X2Args &, hipStream_t);
+template int launch_x2_alt_ct<double>(const Geo &, const X2Args &, hipStream_t);
+template int launch_x2_alt_ct<float>(const Geo &, const X2Args &, hipStream_t);
 
 }  // namespace dft

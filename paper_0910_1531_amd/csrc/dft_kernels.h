@@ -171,7 +171,7 @@ template <typename T> bool launch_y_ct(const Geo &g, const YArgs &a, hipStream_t
 template <typename T> bool launch_z1_ct(const Geo &g, const Z1Args &a, int es, hipStream_t s);
 template <typename T> bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream_t s);
 template <typename T> int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_t s);   // blocks, 0: none
-template <typename T> bool launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s);
+template <typename T> int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s);
 template <typename T> bool launch_x1_ct(const Geo &g, const XFwdArgs &a, hipStream_t s);
 template <typename T> bool launch_x3_ct(const Geo &g, const X3Args &a, hipStream_t s);
 int x_ct_pairs(int nx);        // row pairs per block of the compiled-length x kernels, 0 if none

@@ -144,8 +144,15 @@ constexpr bool yzswz_ok() {
 // (x tiles, whose pencils are rows); elements are swizzled (xswz) against bank conflicts.
 // NB = 2 alternates two LDS buffers (one barrier per exchange); NB = 1 uses one buffer and
 // a second barrier before each write.
-template <typename T, class SC, int P, int NT, bool BF, int NB = 2, int PAD = 0>
+// WV = true: the tile belongs to one wave (NT = 64, the thread index is the lane), so every
+// exchange needs a wave-level fence only, and one buffer is enough: the LDS instructions of a
+// wave execute in order, so its reads of one exchange precede its writes of the next.  The
+// caller passes the lane (t, and in place of the buffer phase ph), and may pass it opaque to the
+// compiler so that the index arithmetic of one transform is not kept in registers for another.
+template <typename T, class SC, int P, int NT, bool BF, int NB = 2, int PAD = 0, bool WV = false>
 struct Fft {
+    static_assert(!WV || (NT == 64 && NB == 1), "a wave's tile has 64 threads and one buffer");
+    __device__ static __forceinline__ int tid() { return WV ? (int)(threadIdx.x & 63) : (int)threadIdx.x; }
     static constexpr int L = SC::L;
     static constexpr int NSTG = SC::n;
     static constexpr int LS = BF ? L + PAD : L;
@@ -176,14 +183,14 @@ struct Fft {
     // LDS regions, and the LDS instructions of one wave execute in order, so a wave-level fence
     // (compiler and memory ordering within the wavefront) replaces the block barrier.
     static constexpr bool wave_private() {
-        if (!BF) return false;
+        if (!BF || WV) return false;
         for (int s = 0; s < NSTG; ++s)
             if (SC::r(s) != 4) return false;
         return items(4) == NT && NT % 64 == 0 && 64 % (L / 4) == 0;
     }
     static constexpr bool WP = wave_private();
     __device__ static __forceinline__ void sync() {
-        if constexpr (WP) {
+        if constexpr (WP || WV) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -218,19 +225,21 @@ struct Fft {
     // Pencil p and element e that register i holds as an input of a first stage (or an
     // output of a last stage) of radix R; false for registers of idle butterflies.
     template <int R>
-    __device__ static __forceinline__ bool pos(int i, int &p, int &e) {
+    __device__ static __forceinline__ bool pos(int i, int &p, int &e, int t) {
         const int it = i / R, q = i - (i / R) * R;
-        const int j = (int)threadIdx.x + it * NT;
+        const int j = t + it * NT;
         int b;
         decode<R>(j, p, b);
         e = b + q * (L / R);
         return exact(R) || j < items(R);
     }
     template <int DIR>
-    __device__ static __forceinline__ bool in_pos(int i, int &p, int &e) { return pos<rad<DIR>(0)>(i, p, e); }
+    __device__ static __forceinline__ bool in_pos(int i, int &p, int &e, int t = tid()) {
+        return pos<rad<DIR>(0)>(i, p, e, t);
+    }
     template <int DIR>
-    __device__ static __forceinline__ bool out_pos(int i, int &p, int &e) {
-        return pos<rad<DIR>(NSTG - 1)>(i, p, e);
+    __device__ static __forceinline__ bool out_pos(int i, int &p, int &e, int t = tid()) {
+        return pos<rad<DIR>(NSTG - 1)>(i, p, e, t);
     }
 
     // Twiddles exp(DIR 2 pi i q k / (NS R)), k = b mod NS, then the radix-R butterflies.
@@ -242,7 +251,7 @@ struct Fft {
             cx<T> *u = v + it * R;
             if constexpr (NS > 1) {
                 int p, b;
-                decode<R>((int)threadIdx.x + it * NT, p, b);
+                decode<R>(tid() + it * NT, p, b);
                 const int k = b % NS;
                 constexpr int ts = L / (NS * R);
 #pragma unroll
@@ -265,7 +274,7 @@ struct Fft {
     __device__ static __forceinline__ void load_twiddles(Twiddles &t, const cx<T> *__restrict__ tw) {
         static_assert(WP, "register twiddles need a wave-private tile");
         int p, b;
-        decode<4>((int)threadIdx.x, p, b);
+        decode<4>(tid(), p, b);
 #pragma unroll
         for (int s = 1; s < NSTG; ++s) {
             const int NS = 1 << (2 * s);
@@ -300,13 +309,13 @@ struct Fft {
         cx<T> w[tw_count<DIR>(NSTG) > 0 ? tw_count<DIR>(NSTG) : 1];
     };
     template <int DIR, int S = 1>
-    __device__ static __forceinline__ void load_tw(TwReg<DIR> &t, const cx<T> *__restrict__ tw) {
+    __device__ static __forceinline__ void load_tw(TwReg<DIR> &t, const cx<T> *__restrict__ tw, int th = tid()) {
         if constexpr (S < NSTG) {
             constexpr int R = rad<DIR>(S), NS = span<DIR>(S), ts = L / (NS * R), o = tw_count<DIR>(S);
 #pragma unroll
             for (int it = 0; it < iters(R); ++it) {
                 int p, b;
-                decode<R>((int)threadIdx.x + it * NT, p, b);
+                decode<R>(th + it * NT, p, b);
                 const int k = b % NS;   // idle butterflies read an in-range entry they never use
 #pragma unroll
                 for (int q = 1; q < R; ++q) {
@@ -315,7 +324,7 @@ struct Fft {
                     t.w[o + it * (R - 1) + q - 1] = w;
                 }
             }
-            load_tw<DIR, S + 1>(t, tw);
+            load_tw<DIR, S + 1>(t, tw, th);
         }
     }
     template <int DIR, int R, int S>
@@ -334,10 +343,10 @@ struct Fft {
 
     // Outputs of a radix-R stage with span NS to the buffer (Stockham order).
     template <int R, int NS>
-    __device__ static __forceinline__ void put(const cx<T> *v, cx<T> *buf) {
+    __device__ static __forceinline__ void put(const cx<T> *v, cx<T> *buf, int t = tid()) {
 #pragma unroll
         for (int it = 0; it < iters(R); ++it) {
-            const int j = (int)threadIdx.x + it * NT;
+            const int j = t + it * NT;
             if (!exact(R) && j >= items(R)) continue;
             int p, b;
             decode<R>(j, p, b);
@@ -349,10 +358,10 @@ struct Fft {
     }
     // Inputs of a radix-R stage from the buffer.
     template <int R>
-    __device__ static __forceinline__ void get(cx<T> *v, const cx<T> *buf) {
+    __device__ static __forceinline__ void get(cx<T> *v, const cx<T> *buf, int t = tid()) {
 #pragma unroll
         for (int it = 0; it < iters(R); ++it) {
-            const int j = (int)threadIdx.x + it * NT;
+            const int j = t + it * NT;
             if (!exact(R) && j >= items(R)) continue;
             int p, b;
             decode<R>(j, p, b);
@@ -374,9 +383,10 @@ struct Fft {
             } else {
                 sync();
             }
-            put<R, NS>(v, buf);
+            const int th = WV ? ph : tid();
+            put<R, NS>(v, buf, th);
             sync();
-            get<rad<DIR>(S + 1)>(v, buf);
+            get<rad<DIR>(S + 1)>(v, buf, th);
             run<DIR, S + 1>(v, lds, ph, t);
         }
     }

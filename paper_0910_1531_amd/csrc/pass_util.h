@@ -158,40 +158,40 @@ __device__ __forceinline__ void block_reduce_nt(double v, int fl, double *dst, i
 }
 
 // ------------------------------------------------------------------ X2 node work
-// Pointwise work of X2 at one real node idx (of N), for eq. (Phi) (ALT = false) or the
+// Pointwise work of X2 at the real node idx0 + j (of N; idx0 the same for all lanes), for eq. (Phi) (ALT = false) or the
 // alternative functional a.hs (ALT = true): the ten weighted densities n in
-// (FP32-mixed: differences from the reference nref), dPhi/dn of eq. (Phi) out in d
-// (FP32-mixed: the difference from dPhi/dn at the reference; X2_HESS: the product
-// Phi''(nstar) n).  Updates the running maximum of n3 and the flags (1: the evaluation is
+// (DIFF, FP32-mixed: differences from the reference nref), dPhi/dn of eq. (Phi) out in d
+// (DIFF: the difference from dPhi/dn at the reference; HESS, the mode X2_HESS: the
+// product Phi''(nstar) n).  Updates the running maximum of n3 and the flags (1: the evaluation is
 // non-finite, 2: xi^2 clamped, 4: n3 itself non-finite) and writes the optional FP64 /
 // FP32 copies.
-template <bool ALT>
-__device__ __forceinline__ void x2_node(const X2Args &a, long long N, long long idx, const double (&nin)[DFT_NALPHA],
+template <bool ALT, bool HESS, bool DIFF>
+__device__ __forceinline__ void x2_node(const X2Args &a, long long N, long long idx0, unsigned j, const double (&nin)[DFT_NALPHA],
                                         double (&d)[DFT_NALPHA], double &mloc, int &flag) {
     double n[DFT_NALPHA];
 #pragma unroll
     for (int f = 0; f < DFT_NALPHA; ++f) n[f] = nin[f];
     bool clamped = false;
-    if (a.mode == X2_HESS) {
+    if constexpr (HESS) {
         Dual nd[DFT_NALPHA], dd[DFT_NALPHA];
 #pragma unroll
-        for (int f = 0; f < DFT_NALPHA; ++f) nd[f] = Dual{a.nstar[f * N + idx], n[f]};
+        for (int f = 0; f < DFT_NALPHA; ++f) nd[f] = Dual{(a.nstar + f * N + idx0)[j], n[f]};
         fmt_dphi_as<ALT, Dual>(a.hs, nd, dd, clamped);
         bool bad = false;
 #pragma unroll
         for (int f = 0; f < DFT_NALPHA; ++f) {
             d[f] = dd[f].d;
             bad |= !isfinite(d[f]);
-            if (a.t_out) a.t_out[f * N + idx] = d[f];
+            if (a.t_out) (a.t_out + f * N + idx0)[j] = d[f];
         }
         if (bad) flag |= 1;
         return;
     }
-    if (a.nref) {
+    if constexpr (DIFF) {
         double nr[DFT_NALPHA], dr[DFT_NALPHA];
 #pragma unroll
         for (int f = 0; f < DFT_NALPHA; ++f) {
-            nr[f] = (double)a.nref[f * N + idx];
+            nr[f] = (double)(a.nref + f * N + idx0)[j];
             n[f] += nr[f];
         }
         bool c2;
@@ -200,18 +200,21 @@ __device__ __forceinline__ void x2_node(const X2Args &a, long long N, long long 
 #pragma unroll
         for (int f = 0; f < DFT_NALPHA; ++f) d[f] -= dr[f];
     } else {
+        // copies of n before the derivatives: fewer values live at once
+#pragma unroll
+        for (int f = 0; f < DFT_NALPHA; ++f) {
+            if (a.nref_out) (a.nref_out + f * N + idx0)[j] = (float)n[f];
+            if (a.n_out) (a.n_out + f * N + idx0)[j] = n[f];
+        }
         fmt_dphi_as<ALT, double>(a.hs, n, d, clamped);
+#pragma unroll
+        for (int f = 0; f < DFT_NALPHA; ++f)
+            if (a.dphi_out) (a.dphi_out + f * N + idx0)[j] = d[f];
     }
     if (clamped) flag |= 2;
     if (!isfinite(n[3])) flag |= 5;                        // 1: evaluation non-finite, 4: n3 non-finite
     if (!isfinite(d[0]) || !isfinite(d[3])) flag |= 1;     // e.g. n3 >= 1: f = +inf, n3 max still valid
     mloc = fmax(mloc, n[3]);
-#pragma unroll
-    for (int f = 0; f < DFT_NALPHA; ++f) {
-        if (a.nref_out) a.nref_out[f * N + idx] = (float)n[f];
-        if (a.n_out) a.n_out[f * N + idx] = n[f];
-        if (a.dphi_out) a.dphi_out[f * N + idx] = d[f];
-    }
 }
 
 // FP64 reciprocal: the hardware estimate refined by one Newton step (error about 1 ulp of FP64).
