@@ -16,8 +16,10 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdftpicard.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
-SOURCES = ["dft_host.cpp", "dft_kernels.hip", "ct_launch_x.hip", "ct_launch_x2.hip", "ct_launch_x2_alt.hip", "ct_launch_y.hip", "ct_launch_z1_f32.hip",
-           "ct_launch_z1_f64.hip", "ct_launch_z2.hip", "dft_tune.hip", "dft_adjoint.hip", "dft_screen.hip", "dft_api.hip"]
+SOURCES = ["dft_host.cpp", "ct_launch_z1_f32.hip", "ct_launch_y_f32.hip", "ct_launch_y_f64.hip", "ct_launch_z1_f64.hip",
+           "ct_launch_z1_more_f32.hip", "ct_launch_z1_more_f64.hip", "ct_launch_x2_f64.hip", "ct_launch_x2_alt_f64.hip",
+           "ct_launch_z2.hip", "ct_launch_x2_f32.hip", "ct_launch_x2_alt_f32.hip", "ct_launch_x.hip", "dft_kernels.hip",
+           "dft_tune.hip", "dft_adjoint.hip", "dft_screen.hip", "dft_api.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -42,7 +44,7 @@ def _compile(src):
 def build(verbose=False):
     """Compile every source and link the shared library; returns its path."""
     os.makedirs(BUILD, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 8)) as ex:
         results = list(ex.map(_compile, SOURCES))
     objs = [o for o, _ in results]
     if verbose:

@@ -40,7 +40,65 @@ __device__ __forceinline__ void static_for(Fn &&f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Lengths whose y and z kernels come in the launch shapes the autotuner chooses among, and those
+// compiled in one shape.
 #define DFT_CT_LENGTHS(X) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384)
+#define DFT_CT_MORE_LENGTHS(X) \
+    X(8) X(9) X(12) X(18) X(27) X(36) X(54) X(72) X(81) X(108) X(144) X(162) X(216) X(243) X(288) X(324) X(432) X(486) \
+    X(512)
+
+// Threads of a tile in the lengths compiled in one shape: of the multiples of 64 up to cap (and of P)
+// that keep at most vcap values per thread in any stage and ocap after the last forward stage, the
+// one that leaves the fewest threads idle over the stages, the larger of equals.
+template <class SC>
+constexpr int one_shape_threads(int P, int cap, int vcap, int ocap) {
+    int best = 0;
+    double least = 1e30;
+    for (int t = 64; t <= cap; t += 64) {
+        if (t % P) continue;
+        bool ok = true;
+        double spent = 0.0;
+        for (int s = 0; s < SC::n; ++s) {
+            const int R = SC::r(s), it = (SC::L * P / R + t - 1) / t;
+            if (it * R > vcap || (s == SC::n - 1 && it * R > ocap)) ok = false;
+            spent += (double)t * it * R;
+        }
+        if (ok && spent <= least) {
+            least = spent;
+            best = t;
+        }
+    }
+    return best;
+}
+
+// ... of a z tile, whose products hold five or six sums of every value after the last forward stage:
+// at most four values where 768 threads allow it, else eight; FP32 up to 162 six values and 512
+// threads (144^3: 64 us either z pass with 192 threads of six values, 90 with 384 of three).
+template <typename T, int L>
+constexpr int z_one_threads(int P) {
+    using SC = typename ct::PlanT<T, L>::type;
+    constexpr int vcap = sizeof(T) == 4 ? 16 : 9;
+    if (sizeof(T) == 4 && L <= 162) return one_shape_threads<SC>(P, 512, vcap, 6);
+    const int few = one_shape_threads<SC>(P, 768, vcap, 4);
+    return few ? few : one_shape_threads<SC>(P, 768, vcap, 8);
+}
+
+// z passes whose index arithmetic is redone at every exchange (Fft's OPQ) instead of held in registers
+// through their seven to ten transforms: the lengths that otherwise spill or leave one wave per SIMD.
+// Measured on 64 x 64 x n_z, three species, us held / redone: FP64 Z1 192 56 / 43, 384 109 / 96,
+// 432 253 / 113, 144 55 / 50, 256 50 / 47 (256^3 788 / 773); Z2 192 71 / 51, 432 209 / 116,
+// 96 28 / 46, 256^3 790 / 823; FP32 Z1 432 107 / 48, 324 67 / 58, 256 38 / 41; Z2 432 133 / 53,
+// 512 69 / 54, 324 58 / 80.
+template <typename T, int L>
+constexpr bool z1_redo() {
+    if (sizeof(T) == 8) return L == 144 || L == 162 || L == 192 || L == 256 || L == 384 || L == 432 || L == 486;
+    return L == 324 || L == 432 || L == 486;
+}
+template <typename T, int L>
+constexpr bool z2_redo() {
+    if (sizeof(T) == 8) return L == 192 || L == 432 || L == 486;
+    return L == 432 || L == 486 || L == 512;
+}
 
 // ------------------------------------------------------------------ y / z plain transforms
 // One block transforms P adjacent pencils of one field along y or z; the pencils' elements sit
@@ -516,7 +574,7 @@ __device__ __forceinline__ void z1_inverse(const Geo &g, const Z1Args &a, const 
 
 template <typename T, int L, int P, int NTB, int MS>
 __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
-    using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2>;
+    using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z1_redo<T, L>()>;
     constexpr int NO = F::template nout<-1>();
     static_assert(NO == F::template nin<1>(), "inverse must start where the forward ends");
     constexpr bool TAB = std::is_same<T, double>::value;
@@ -619,7 +677,7 @@ __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
 // after reading them.
 template <typename T, int L, int P, int NTB, int MS>
 __global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
-    using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2>;
+    using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z1_redo<T, L>()>;
     constexpr int NO = F::template nin<1>();
     constexpr bool TAB = std::is_same<T, double>::value;
     const int prob = (int)blockIdx.z;
@@ -694,7 +752,7 @@ __global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
 // Weights: tables in FP64, on the fly in FP32.
 template <typename T, int L, int P, int NTB>
 __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
-    using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2>;
+    using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z2_redo<T, L>()>;
     constexpr int NO = F::template nout<-1>();
     static_assert(NO == F::template nin<1>(), "inverse must start where the forward ends");
     constexpr bool TAB = std::is_same<T, double>::value;
@@ -923,301 +981,6 @@ __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
         }
         inv_store(reinterpret_cast<cx<T> *>(a.specA) + (long long)is * NC + off);
     }
-}
-
-// ------------------------------------------------------------------ x passes
-// Two real rows (r0, r0 + 1) travel as the real and imaginary parts of one complex row:
-// the forward transform C of c = a + i b gives A_k = (C_k + conj C_{L-k}) / 2 and
-// B_k = (C_k - conj C_{L-k}) / (2i); the inverse rebuilds C from the Hermitian halves.
-// A tile holds PB such row pairs; the block has PB L / 4 threads, and with the x schedules
-// (radices <= 4, forward starting with 4) each thread ends an inverse transform holding
-// the same four columns of its pencil for every field, so the nodewise work of X2 runs on
-// registers.
-template <int L>
-struct XTile {
-    static constexpr int PB = (L % 3 == 0) ? 768 / L : 1024 / L;
-    static constexpr int NTB = PB * L / 4;
-    static constexpr int KX = L / 2 + 1;
-    static constexpr int PAD = 0;
-};
-
-// Element e of the full spectrum of a real row from its half spectrum (Hermitian).
-template <typename T, int L>
-__device__ __forceinline__ cx<T> half_at(const cx<T> *row, int e) {
-    constexpr int KX = L / 2 + 1;
-    cx<T> v;
-    if (e < KX) {
-        v = ct::gld(row + e);
-        if (e == 0 || 2 * e == L) v.y = T(0);
-    } else {
-        v = conjg(ct::gld(row + (L - e)));
-    }
-    return v;
-}
-
-// Value v of lane src of the wave (cross-lane permute, 32 bits at a time; no memory access).
-template <typename T>
-__device__ __forceinline__ cx<T> lane_value(cx<T> v, int src) {
-    constexpr int W = (int)(sizeof(cx<T>) / 4);
-    int w[W];
-    __builtin_memcpy(w, &v, sizeof(v));
-#pragma unroll
-    for (int k = 0; k < W; ++k) w[k] = __builtin_amdgcn_ds_bpermute(src << 2, w[k]);
-    cx<T> r;
-    __builtin_memcpy(&r, w, sizeof(r));
-    return r;
-}
-
-// Inputs of an inverse x transform: for the row pair of register i, C_e = A_e + i B_e from the
-// half spectra of rows r0 and r0 + 1 (B = 0 past the last row; pairs past Pact read as zero).
-// In a wave-private tile lane b of a pencil holds e = b + q L/4 (q = 0..3); the elements
-// e > L/2 are conj(A_{L-e}), and L - e is an element that lane (L/4 - b) mod L/4 of the same
-// pencil loads for q = 0 or 1, so they come by cross-lane permutes instead of second loads.
-template <typename T, int L, class F>
-__device__ __forceinline__ void load_row_pairs(const cx<T> *in, long long pair0, int Pact, long long rows, cx<T> *c) {
-    constexpr int KX = L / 2 + 1;
-    if constexpr (F::WP) {
-        constexpr int Q = L / 4;
-        static_assert(F::template nin<1>() == 4, "one radix-4 butterfly per thread");
-        int p, b;
-        F::template in_pos<1>(0, p, b);
-        const bool ok = p < Pact;
-        const long long r0 = 2 * (pair0 + p);
-        const bool okb = ok && r0 + 1 < rows;
-        const cx<T> *ra = in + r0 * KX, *rb = ra + KX;
-        const cx<T> z = mk<T>(T(0), T(0));
-        cx<T> A0 = z, A1 = z, An = z, B0 = z, B1 = z, Bn = z;
-        if (ok) {
-            A0 = ct::gld(ra + b);
-            A1 = ct::gld(ra + Q + b);
-            if (b == 0) {
-                A0.y = T(0);
-                An = ct::gld(ra + 2 * Q);   // the Nyquist element
-                An.y = T(0);
-            }
-        }
-        if (okb) {
-            B0 = ct::gld(rb + b);
-            B1 = ct::gld(rb + Q + b);
-            if (b == 0) {
-                B0.y = T(0);
-                Bn = ct::gld(rb + 2 * Q);
-                Bn.y = T(0);
-            }
-        }
-        const int lane = (int)(threadIdx.x & 63);
-        const int src = lane - b + ((Q - b) & (Q - 1));
-        const cx<T> a1 = lane_value(A1, src), a0 = lane_value(A0, src);
-        const cx<T> b1 = lane_value(B1, src), b0 = lane_value(B0, src);
-        const cx<T> A2 = b == 0 ? An : conjg(a1), A3 = b == 0 ? conjg(a1) : conjg(a0);
-        const cx<T> B2 = b == 0 ? Bn : conjg(b1), B3 = b == 0 ? conjg(b1) : conjg(b0);
-        c[0] = mk<T>(A0.x - B0.y, A0.y + B0.x);
-        c[1] = mk<T>(A1.x - B1.y, A1.y + B1.x);
-        c[2] = mk<T>(A2.x - B2.y, A2.y + B2.x);
-        c[3] = mk<T>(A3.x - B3.y, A3.y + B3.x);
-    } else {
-#pragma unroll
-        for (int i = 0; i < F::template nin<1>(); ++i) {
-            int p, e;
-            const bool ok = F::template in_pos<1>(i, p, e) && p < Pact;
-            cx<T> cv = mk<T>(T(0), T(0));
-            if (ok) {
-                const long long r0 = 2 * (pair0 + p);
-                const cx<T> A = half_at<T, L>(in + r0 * KX, e);
-                cx<T> B = mk<T>(T(0), T(0));
-                if (r0 + 1 < rows) B = half_at<T, L>(in + (r0 + 1) * KX, e);
-                cv = mk<T>(A.x - B.y, A.y + B.x);
-            }
-            c[i] = cv;
-        }
-    }
-}
-
-// Half spectra of the two real rows of every row pair from the forward transform of the pair
-// (C held in split): A_k = (C_k + conj C_{L-k}) / 2, B_k = (C_k - conj C_{L-k}) / (2i).  In a
-// wave-private tile each wave splits its own pencils (lanes along k); otherwise the block does
-// (split must have been synchronized accordingly by the caller).
-template <typename T, int L, class F>
-__device__ __forceinline__ void split_rows(const cx<T> *split, cx<T> *out, long long pair0, int Pact, long long rows) {
-    constexpr int KX = L / 2 + 1;
-    auto coeffs = [&](int p, int k, cx<T> &A, cx<T> &B) {
-        const cx<T> ck = split[F::lidx(p, k)];
-        const cx<T> cm = split[F::lidx(p, k == 0 ? 0 : L - k)];
-        A = mk<T>(T(0.5) * (ck.x + cm.x), T(0.5) * (ck.y - cm.y));
-        B = mk<T>(T(0.5) * (ck.y + cm.y), T(-0.5) * (ck.x - cm.x));
-    };
-    auto one = [&](int p, int k) {
-        cx<T> A, B;
-        coeffs(p, k, A, B);
-        const long long r0 = 2 * (pair0 + p);
-        ct::gst(out + r0 * KX + k, A);
-        if (r0 + 1 < rows) ct::gst(out + (r0 + 1) * KX + k, B);
-    };
-    if constexpr (F::WP) {
-        // lane b of a pencil writes k = b and b + L/4 of both rows; the Nyquist element k = L/2
-        // goes to row r0 from lane 0 and to row r0 + 1 from lane 1 (one store instead of two)
-        constexpr int nb = L / 4;
-        const int lane = (int)threadIdx.x % 64;
-        const int p = ((int)threadIdx.x / 64) * (64 / nb) + lane / nb;
-        const int b = lane % nb;
-        if (p < Pact) {
-            one(p, b);
-            one(p, b + nb);
-            if (b < 2) {
-                cx<T> A, B;
-                coeffs(p, 2 * nb, A, B);
-                const long long r = 2 * (pair0 + p) + b;
-                if (r < rows) ct::gst(out + r * KX + 2 * nb, b == 0 ? A : B);
-            }
-        }
-    } else {
-        for (int j = threadIdx.x; j < Pact * KX; j += (int)blockDim.x) {
-            const int p = j / KX;
-            one(p, j - p * KX);
-        }
-    }
-}
-
-// X1: real rows of field blockIdx.y (plain, or the line-search trial point
-// rho0 + alpha (g0 - rho0), written out; FP32-mixed: minus the reference) -> forward x ->
-// half spectra.
-template <typename T, int L>
-__global__ __launch_bounds__(XTile<L>::NTB) void k_x1c(Geo g_in, XFwdArgs a) {
-    using XT = XTile<L>;
-    constexpr int PB = XT::PB, NTB = XT::NTB;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PB, NTB, true, 2, XT::PAD>;
-    const int prob = (int)blockIdx.z;
-    if (prob > 0) {
-        const long long o = (long long)prob * g_in.pstride;
-        g_in = shift(g_in, o);
-        a = shift(a, o);
-    }
-    const Geo &g = g_in;
-    if (gated_off(a.gate)) return;
-    resolve_roles(a);
-    // wave-private tiles: twiddles fetched up front, with the data
-    typename F::Twiddles trw;
-    if constexpr (F::WP) F::load_twiddles(trw, twp<T>(g_in, 0));
-    __shared__ cx<T> lds[F::LDS_ELEMS + F::TILE];
-    cx<T> *split = lds + F::LDS_ELEMS;
-    const int f = blockIdx.y;
-    const long long rows = (long long)g.ny * g.nz;
-    const long long npairs = (rows + 1) / 2;
-    const long long pair0 = (long long)blockIdx.x * PB;
-    const int Pact = (int)min((long long)PB, npairs - pair0);
-    const long long foff = (long long)f * g.N;
-    const bool trial = a.mode == XF_TRIAL;
-    const double alpha = trial ? *a.alpha : 0.0;
-    cx<T> v[F::V];
-#pragma unroll
-    for (int i = 0; i < F::template nin<-1>(); ++i) {
-        int p, e;
-        const bool ok = F::template in_pos<-1>(i, p, e) && p < Pact;
-        double x[2] = {0.0, 0.0};
-        if (ok) {
-            const long long r0 = 2 * (pair0 + p);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const long long r = r0 + h;
-                if (r >= rows) break;
-                const long long idx = foff + r * L + e;
-                double xv;
-                if (trial) {
-                    const double r0v = ct::cld(a.src + idx);
-                    xv = fma(alpha, ct::cld(a.g0 + idx) - r0v, r0v);
-                    if (a.rho_t) ct::gst(a.rho_t + idx, xv);
-                } else {
-                    xv = ct::cld(a.src + idx);
-                }
-                if (a.ref) xv -= ct::cld(a.ref + idx);
-                x[h] = xv;
-            }
-        }
-        v[i] = mk<T>(T(x[0]), T(x[1]));
-    }
-    int ph = 0;
-    if constexpr (F::WP) F::template run<-1>(v, lds, ph, trw);
-    else F::template run<-1>(v, lds, ph, twp<T>(g, 0));
-#pragma unroll
-    for (int i = 0; i < F::template nout<-1>(); ++i) {
-        int p, e;
-        if (F::template out_pos<-1>(i, p, e)) split[F::lidx(p, e)] = v[i];
-    }
-    F::sync();
-    split_rows<T, L, F>(split, reinterpret_cast<cx<T> *>(a.spec) + (long long)f * g.NC, pair0, Pact, rows);
-}
-
-// X3: half spectra of E_k (species blockIdx.y) -> inverse x -> Euler-Lagrange update
-// G = rho_b exp(base + E) (eq. rhoEquation) and the weighted residual sums; raw mode
-// writes E (+ addend) only.
-template <typename T, int L>
-__global__ __launch_bounds__(XTile<L>::NTB) void k_x3c(Geo g_in, X3Args a) {
-    using XT = XTile<L>;
-    constexpr int PB = XT::PB, NTB = XT::NTB;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PB, NTB, true, 2, XT::PAD>;
-    const int prob = (int)blockIdx.z;
-    if (prob > 0) {
-        const long long o = (long long)prob * g_in.pstride;
-        g_in = shift(g_in, o);
-        a = shift(a, o);
-    }
-    const Geo &g = g_in;
-    if (gated_off(a.gate)) return;
-    resolve_roles(a);
-    // wave-private tiles: twiddles fetched up front, with the data
-    typename F::Twiddles trw;
-    if constexpr (F::WP) F::load_twiddles(trw, twp<T>(g_in, 0));
-    __shared__ cx<T> lds[F::LDS_ELEMS];
-    const Consts &c = *g.cs;
-    const int sp = blockIdx.y;
-    const long long N = g.N;
-    const long long rows = (long long)g.ny * g.nz;
-    const long long npairs = (rows + 1) / 2;
-    const long long pair0 = (long long)blockIdx.x * PB;
-    const int Pact = (int)min((long long)PB, npairs - pair0);
-    const cx<T> *in = reinterpret_cast<const cx<T> *>(a.specA) + (long long)sp * g.NC;
-    cx<T> v[F::V];
-    load_row_pairs<T, L, F>(in, pair0, Pact, rows, v);
-    int ph = 0;
-    if constexpr (F::WP) F::template run<1>(v, lds, ph, trw);
-    else F::template run<1>(v, lds, ph, twp<T>(g, 0));
-    double acc = 0.0;
-    int flag = 0;
-    const double rb = c.rho_b[sp], irb = c.inv_rho_b[sp], zs = c.z[sp];
-#pragma unroll
-    for (int i = 0; i < F::template nout<1>(); ++i) {
-        int p, e;
-        if (!(F::template out_pos<1>(i, p, e) && p < Pact)) continue;
-        const long long r0 = 2 * (pair0 + p);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const long long r = r0 + h;
-            if (r >= rows) break;
-            const double E = h == 0 ? (double)v[i].x : (double)v[i].y;
-            const long long node = r * L + e;
-            const long long idx = (long long)sp * N + node;
-            if (a.raw) {
-                double o = E;
-                if (a.addend) o += ct::gld(a.addend + node);
-                ct::gst(a.raw_out + idx, o);
-                continue;
-            }
-            const double b = ct::cld(a.base + idx);
-            const bool fluid = b > -INFINITY;
-            const double G = fluid ? rb * exp(b + E) : 0.0;
-            if (a.g_out) ct::gst(a.g_out + idx, G);
-            if (a.e_out) ct::gst(a.e_out + idx, a.e_phi ? E - zs * ct::gld(a.e_phi + node) : E);
-            if (a.lp_out) ct::gst(a.lp_out + idx, fluid ? b + E : -INFINITY);
-            if (fluid) {
-                const double dlt = (ct::cld(a.rho_t + idx) - G) * irb;
-                acc += dlt * dlt;
-                if (!isfinite(G)) flag |= 1;
-            }
-        }
-    }
-    if (a.raw) return;
-    const long long slot = (long long)blockIdx.y * gridDim.x + blockIdx.x;
-    block_reduce_nt<false, NTB>(acc, flag, a.red.fpart + slot, a.red.fflag + slot);
 }
 
 }  // namespace dft

@@ -52,6 +52,15 @@ static void launch_z2c_var(const Geo &g, const Z2Args &a, hipStream_t s) {
     ct_check("z2 (compiled length)");
 }
 
+// The one shape of the lengths outside DFT_CT_LENGTHS: shape 0's columns.
+template <typename T, int L>
+static void launch_z2c_one(const Geo &g, const Z2Args &a, hipStream_t s) {
+    constexpr int P = z2_width<T>(0), NTB = z_one_threads<T, L>(P);
+    dim3 grid((unsigned)ct_cdiv(g.ny * g.Kx, P), 1, (unsigned)g.nprob);   // flattened (y, kx) columns
+    hipLaunchKernelGGL((k_z2c<T, L, P, NTB>), grid, dim3(NTB), 0, s, g, a);
+    ct_check("z2 (compiled length)");
+}
+
 template <typename T>
 bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream_t s) {
     if (!g.tab64) return false;   // no spectral tables: run-time-length kernel
@@ -65,6 +74,9 @@ bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream_t s) {
         return true;
         DFT_CT_LENGTHS(DFT_CASE)
 #undef DFT_CASE
+#define DFT_CASE(n) case n: launch_z2c_one<T, n>(g, a, s); return true;
+        DFT_CT_MORE_LENGTHS(DFT_CASE)
+#undef DFT_CASE
         default: return false;
     }
 }
@@ -75,13 +87,19 @@ int z_ct_variants(int L) {
 #define DFT_CASE(n) case n: return 3;
         DFT_CT_LENGTHS(DFT_CASE)
 #undef DFT_CASE
+#define DFT_CASE(n) case n: return 1;
+        DFT_CT_MORE_LENGTHS(DFT_CASE)
+#undef DFT_CASE
         default: return 0;
     }
 }
 
 // Z1 shapes: the three fused tile widths, then the same widths split into the plain z pass and
-// k_z1s.
-int z1_ct_variants(int L) { return 2 * z_ct_variants(L); }
+// k_z1s (fused only in the lengths compiled in one shape).
+int z1_ct_variants(int L) {
+    const int n = z_ct_variants(L);
+    return n > 1 ? 2 * n : n;
+}
 
 int spec_table_rows(int nz, int S, int es) {
     if (z_ct_variants(nz) == 0) return 0;

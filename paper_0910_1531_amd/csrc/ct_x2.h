@@ -2,7 +2,7 @@
 // pointwise dPhi/dn (eq. Phi) -> forward x -> half spectra, in place in specB.
 #pragma once
 
-#include "ct_kernels.h"
+#include "ct_rows.h"
 
 namespace dft {
 
@@ -16,26 +16,14 @@ enum X2Node { X2N_FP64 = 0, X2N_D32 = 1, X2N_ALT = 2, X2N_HESS = 3, X2N_HESS_ALT
 // share the nodes of the block, one real node each, and the waves transform their fields back.  Bound
 // by the latency of one block's chain, which has two transforms one after the other (a block that
 // held all ten fields in registers ran twenty: 24^3 56 us, 48^3 62 us; now 13 and 15).
-template <int L>
-struct XWide {
-    static constexpr int PW = 256 / L > 0 ? 256 / L : 1;   // pencils of a wave: as many as one radix-4 butterfly
-                                                           // per lane covers
-    static constexpr int NTB = 64 * DFT_NALPHA;
-};
-
-// Element at a 32-bit byte offset of a base that all lanes share: the base stays in scalar registers
-// and a lane holds one register of address.
-template <typename V>
-__device__ __forceinline__ V *at(V *base, unsigned off) {
-    return reinterpret_cast<V *>(reinterpret_cast<char *>(const_cast<typename std::remove_const<V>::type *>(base)) + off);
-}
+constexpr int kX2WideThreads = 64 * DFT_NALPHA;
 
 template <typename T, int L, int NODE>
-__global__ __launch_bounds__(XWide<L>::NTB) __attribute__((amdgpu_waves_per_eu(3))) void
+__global__ __launch_bounds__(kX2WideThreads) __attribute__((amdgpu_waves_per_eu(3))) void
 k_x2w(Geo g_in, X2Args a) {
-    using XW = XWide<L>;
-    constexpr int PW = XW::PW, NTB = XW::NTB, KX = L / 2 + 1;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PW, 64, true, 1, 0, true>;
+    using X = XRow<L>;
+    using F = typename X::template F<T>;
+    constexpr int PW = X::PW, NTB = kX2WideThreads, KX = X::KX;
     constexpr bool D32 = NODE == X2N_D32, ALT = NODE == X2N_ALT || NODE == X2N_HESS_ALT;
     constexpr bool HESS = NODE == X2N_HESS || NODE == X2N_HESS_ALT;
     static_assert(!D32 || std::is_same<T, float>::value, "FP32 difference path");
@@ -66,18 +54,8 @@ k_x2w(Geo g_in, X2Args a) {
     // half spectra of the row pairs, every load in flight together
     const cx<T> *in = reinterpret_cast<const cx<T> *>(a.specB) + (long long)(from_n3 ? 3 : f) * NC + 2 * pair0 * KX;
     const int rows_here = (int)min((long long)(2 * PW), rows - 2 * pair0);   // real rows of the block
-    constexpr unsigned CB = sizeof(cx<T>);
-    constexpr int NIT = (PW * KX + 63) / 64;
-    cx<T> A[NIT], B[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int j = lane + it * 64;
-        const int p = j / KX, k = j - p * KX;
-        const unsigned o = (unsigned)(2 * p * KX + k) * CB;
-        A[it] = B[it] = mk<T>(T(0), T(0));
-        if (2 * p < rows_here) A[it] = ct::gld(at(in, o));
-        if (2 * p + 1 < rows_here) B[it] = ct::gld(at(in, o + KX * CB));
-    }
+    HalfRows<T, L> half;
+    half.load(in, rows_here, lane);
     typename F::template TwReg<1> tri;
     F::template load_tw<1>(tri, tw, lane);
     // real node of thread m: row h = m % 2 of its pair, element e
@@ -98,17 +76,7 @@ k_x2w(Geo g_in, X2Args a) {
             nr[q] = 2 * p + h < rows_here ? ct::cld(at(a.nref + q * N + idx0, o)) : 0.0f;
     };
     if constexpr (D32) fetch_nref((int)threadIdx.x);
-    // C = A + i B on the full length: element L - k holds conj(A_k) + i conj(B_k)
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int j = lane + it * 64;
-        const int p = j / KX, k = j - p * KX;
-        if (p >= PW) continue;
-        const bool self = k == 0 || 2 * k == L;   // its own mirror image: the imaginary parts vanish
-        if (self) A[it].y = B[it].y = T(0);
-        tile[F::lidx(p, k)] = mk<T>(A[it].x - B[it].y, A[it].y + B[it].x);
-        if (!self) tile[F::lidx(p, L - k)] = mk<T>(A[it].x + B[it].y, -A[it].y + B[it].x);
-    }
+    half.put(tile, lane);
     F::sync();
     cx<T> v[F::V];
     F::template get<F::template rad<1>(0)>(v, tile, lane);
@@ -176,28 +144,9 @@ k_x2w(Geo g_in, X2Args a) {
         if (F::template out_pos<-1>(i, p, e, lane)) tile[F::lidx(p, e)] = v[i];
     }
     F::sync();
-    // half spectra of the two rows, A_k = (C_k + conj C_{L-k}) / 2, B_k = (C_k - conj C_{L-k}) / (2i);
     // compact layout: the x components of the vector derivatives leave multiplied by i k_x
-    cx<T> *out = reinterpret_cast<cx<T> *>(a.specB) + (long long)f * NC + 2 * pair0 * KX;
-    const bool times_ikx = g.compact && (f == 4 || f == 7);
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-        const int j = lane + it * 64;
-        const int p = j / KX, k = j - p * KX;
-        if (2 * p >= rows_here) continue;
-        const cx<T> ck = tile[F::lidx(p, k)];
-        const cx<T> cm = tile[F::lidx(p, k == 0 ? 0 : L - k)];
-        cx<T> Ak = mk<T>(T(0.5) * (ck.x + cm.x), T(0.5) * (ck.y - cm.y));
-        cx<T> Bk = mk<T>(T(0.5) * (ck.y + cm.y), T(-0.5) * (ck.x - cm.x));
-        if (times_ikx) {
-            const T kx = (L % 2 == 0 && 2 * k == L) ? T(0) : T(k) * dk0;
-            Ak = mk<T>(-kx * Ak.y, kx * Ak.x);
-            Bk = mk<T>(-kx * Bk.y, kx * Bk.x);
-        }
-        const unsigned o = (unsigned)(2 * p * KX + k) * CB;
-        ct::gst(at(out, o), Ak);
-        if (2 * p + 1 < rows_here) ct::gst(at(out, o + KX * CB), Bk);
-    }
+    store_half_rows<T, L>(tile, reinterpret_cast<cx<T> *>(a.specB) + (long long)f * NC + 2 * pair0 * KX, rows_here, lane,
+                          g.compact && (f == 4 || f == 7), dk0);
 }
 
 // Large grids.  The ten fields of a row pair shared by two waves of the block.  Wave h of a pair transforms the
@@ -285,19 +234,24 @@ __device__ __forceinline__ void x2h_swap_and_nodes(const X2Args &a, long long N,
     F::sync();   // the reads above precede the transforms' writes to the same region
 }
 
-// Waves per SIMD the registers allow without (or with few) spills: FP32 126 registers; FP64 about 200,
-// or 168 with 6 spilled at the lengths whose lanes are partly idle.  n_x = 384 holds eight values a
-// field.  Measured in FP64: 96^3 63 us at two waves, 55 at three; 256^3 699 at two, 816 at three.
-template <typename T, int L>
+// Waves per SIMD that the registers allow without (or with few) spills, by the values a field has per
+// lane (four, six or eight) and the nodewise form: FP32 differences 126 registers; FP64 about 200, or
+// 168 with 6 spilled at the lengths whose lanes are partly idle.  Measured in FP64: 96^3 63 us at two
+// waves, 55 at three; 256^3 699 at two, 816 at three.
+template <typename T, int L, int NODE>
 struct XHalf {
-    static constexpr int WPE = sizeof(T) == 4 ? (L > 256 ? 2 : 4) : (L > 256 ? 1 : (L == 96 || L == 192) ? 3 : 2);
+    static constexpr int NV = XRow<L>::template F<T>::template nout<1>();
+    static constexpr int WPE = NODE == X2N_D32 ? (NV <= 4 ? 4 : NV <= 6 ? 3 : 2)
+                               : sizeof(T) == 4 ? 2
+                                                : (NV > 6 ? 1 : (L == 96 || L == 192) ? 3 : 2);
 };
 
 template <typename T, int L, int NODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XHalf<T, L>::WPE))) void
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(XHalf<T, L, NODE>::WPE))) void
 k_x2h(Geo g_in, X2Args a) {
-    constexpr int PW = XWide<L>::PW, KX = L / 2 + 1;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PW, 64, true, 1, 0, true>;
+    using X = XRow<L>;
+    using F = typename X::template F<T>;
+    constexpr int PW = X::PW, KX = X::KX;
     constexpr int NV = F::template nout<1>();
     static_assert(NV == F::template nin<-1>() && NV % 2 == 0, "registers of a node are the same in both directions");
     const int prob = (int)blockIdx.z;
@@ -322,30 +276,14 @@ k_x2h(Geo g_in, X2Args a) {
     const int rows_here = (int)max(0LL, min((long long)(2 * PW), rows - 2 * pair0));   // real rows of the wave
     const cx<T> *tw = twp<T>(g, 0);
     const T dk0 = T(g.cs->dk[0]);   // k_x step, read before any store
-    constexpr unsigned CB = sizeof(cx<T>);
-    // elements below L/2 of both rows of every pair, then the Nyquist elements, one row a lane
-    constexpr int KH = (L + 1) / 2, NIT = (PW * KH + 63) / 64;
-    constexpr bool EVEN = L % 2 == 0;
-    static_assert(2 * PW <= 64, "one lane per row for the Nyquist elements");
-    const cx<T> z = mk<T>(T(0), T(0));
-    cx<T> A[5][NIT], B[5][NIT], Q[5];
+    HalfRows<T, L> half[5];
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
         const int f = h == 0 ? x2_half_field(0, j) : x2_half_field(1, j);
         // compact layout: n_V2,x = -i k_x n3 is formed below from field 3
         const bool skip = f == 7 && g.compact;
-        const cx<T> *in = reinterpret_cast<const cx<T> *>(a.specB) + (long long)f * NC + 2 * pair0 * KX;
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int i = lane + it * 64;
-            const int p = i / KH, k = i - p * KH;
-            const unsigned o = (unsigned)(2 * p * KX + k) * CB;
-            A[j][it] = B[j][it] = z;
-            if (!skip && 2 * p < rows_here) A[j][it] = ct::gld(at(in, o));
-            if (!skip && 2 * p + 1 < rows_here) B[j][it] = ct::gld(at(in, o + KX * CB));
-        }
-        Q[j] = z;
-        if (EVEN && !skip && lane < rows_here) Q[j] = ct::gld(at(in, (unsigned)(lane * KX + L / 2) * CB));
+        half[j].load(reinterpret_cast<const cx<T> *>(a.specB) + (long long)f * NC + 2 * pair0 * KX, skip ? 0 : rows_here,
+                     lane);
     }
     typename F::template TwReg<1> tri;
     F::template load_tw<1>(tri, tw, lane);
@@ -359,26 +297,12 @@ k_x2h(Geo g_in, X2Args a) {
             for (int i = 0; i < F::template nin<1>(); ++i) {
                 int p, e;
                 F::template in_pos<1>(i, p, e, lane);
-                const T kx = (EVEN && 2 * e == L) ? T(0) : T(e <= L / 2 ? e : e - L) * dk0;
+                const T kx = (X::EVEN && 2 * e == L) ? T(0) : T(e <= L / 2 ? e : e - L) * dk0;
                 v[i] = mk<T>(kx * v3[i].y, -kx * v3[i].x);
             }
         } else {
-            // C = A + i B on the full length: element L - k holds conj(A_k) + i conj(B_k)
             F::sync();
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const int i = lane + it * 64;
-                const int p = i / KH, k = i - p * KH;
-                if (p >= PW) continue;
-                cx<T> Ak = A[j][it], Bk = B[j][it];
-                if (k == 0) Ak.y = Bk.y = T(0);
-                tile[F::lidx(p, k)] = mk<T>(Ak.x - Bk.y, Ak.y + Bk.x);
-                if (k > 0) tile[F::lidx(p, L - k)] = mk<T>(Ak.x + Bk.y, -Ak.y + Bk.x);
-            }
-            if constexpr (EVEN) {
-                // Nyquist: real parts of the even (real) and odd (imaginary) row
-                if (lane < 2 * PW) reinterpret_cast<T *>(&tile[F::lidx(lane >> 1, L / 2)])[lane & 1] = Q[j].x;
-            }
+            half[j].put(tile, lane);
             F::sync();
             F::template get<F::template rad<1>(0)>(v, tile, lane);
             if (h == 0 && j == 3) {
@@ -413,37 +337,10 @@ k_x2h(Geo g_in, X2Args a) {
             if (F::template out_pos<-1>(i, p, e, lane)) tile[F::lidx(p, e)] = v[i];
         }
         F::sync();
-        // half spectra of the two rows, A_k = (C_k + conj C_{L-k}) / 2, B_k = (C_k - conj C_{L-k}) / (2i);
         // compact layout: the x components of the vector derivatives leave multiplied by i k_x
         const int f = h == 0 ? x2_half_field(0, j) : x2_half_field(1, j);
-        cx<T> *out = reinterpret_cast<cx<T> *>(a.specB) + (long long)f * NC + 2 * pair0 * KX;
-        const bool times_ikx = g.compact && (f == 4 || f == 7);
-#pragma unroll
-        for (int it = 0; it < NIT; ++it) {
-            const int i = lane + it * 64;
-            const int p = i / KH, k = i - p * KH;
-            if (2 * p >= rows_here) continue;
-            const cx<T> ck = tile[F::lidx(p, k)];
-            const cx<T> cm = tile[F::lidx(p, k == 0 ? 0 : L - k)];
-            cx<T> Ak = mk<T>(T(0.5) * (ck.x + cm.x), T(0.5) * (ck.y - cm.y));
-            cx<T> Bk = mk<T>(T(0.5) * (ck.y + cm.y), T(-0.5) * (ck.x - cm.x));
-            if (times_ikx) {
-                const T kx = T(k) * dk0;
-                Ak = mk<T>(-kx * Ak.y, kx * Ak.x);
-                Bk = mk<T>(-kx * Bk.y, kx * Bk.x);
-            }
-            const unsigned o = (unsigned)(2 * p * KX + k) * CB;
-            ct::gst(at(out, o), Ak);
-            if (2 * p + 1 < rows_here) ct::gst(at(out, o + KX * CB), Bk);
-        }
-        if constexpr (EVEN) {
-            if (lane < rows_here) {
-                const cx<T> c = tile[F::lidx(lane >> 1, L / 2)];
-                const T re = (lane & 1) ? c.y : c.x;
-                // (C_k + conj C_k) / 2 and (C_k - conj C_k) / (2i) of an element that is its own mirror
-                ct::gst(at(out, (unsigned)(lane * KX + L / 2) * CB), times_ikx ? z : mk<T>(T(0.5) * (re + re), T(0)));
-            }
-        }
+        store_half_rows<T, L>(tile, reinterpret_cast<cx<T> *>(a.specB) + (long long)f * NC + 2 * pair0 * KX, rows_here,
+                              lane, g.compact && (f == 4 || f == 7), dk0);
     }
 }
 
@@ -451,8 +348,9 @@ k_x2h(Geo g_in, X2Args a) {
 // Four waves, each with its own pencils.
 template <typename T, int L>
 __global__ __launch_bounds__(256) void k_x2n(Geo g_in, X2Args a) {
-    constexpr int PW = XWide<L>::PW, KX = L / 2 + 1;
-    using F = ct::Fft<T, typename ct::XPlan<L>::type, PW, 64, true, 1, 0, true>;
+    using X = XRow<L>;
+    using F = typename X::template F<T>;
+    constexpr int PW = X::PW, KX = X::KX;
     const int prob = (int)blockIdx.z;
     if (prob > 0) {
         const long long o = (long long)prob * g_in.pstride;
@@ -462,27 +360,15 @@ __global__ __launch_bounds__(256) void k_x2n(Geo g_in, X2Args a) {
     const Geo &g = g_in;
     if (gated_off(a.gate)) return;
     __shared__ cx<T> lds[4 * F::TILE];
-    const int w = (int)threadIdx.x / 64, lane = (int)threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = (int)threadIdx.x & 63;
     cx<T> *tile = lds + w * F::TILE;
     const long long N = g.N;
     const long long rows = (long long)g.ny * g.nz;
-    const long long npairs = (rows + 1) / 2;
     const long long pair0 = ((long long)blockIdx.x * 4 + w) * PW;
-    const int Pact = (int)max(0LL, min((long long)PW, npairs - pair0));
-    const cx<T> *in = reinterpret_cast<const cx<T> *>(a.specB);
-    for (int j = lane; j < PW * KX; j += 64) {
-        const int p = j / KX, k = j - p * KX;
-        const long long r0 = 2 * (pair0 + p);
-        cx<T> A = mk<T>(T(0), T(0)), B = A;
-        if (p < Pact) {
-            A = ct::gld(in + r0 * KX + k);
-            if (r0 + 1 < rows) B = ct::gld(in + (r0 + 1) * KX + k);
-        }
-        const bool self = k == 0 || 2 * k == L;
-        if (self) A.y = B.y = T(0);
-        tile[F::lidx(p, k)] = mk<T>(A.x - B.y, A.y + B.x);
-        if (!self) tile[F::lidx(p, L - k)] = mk<T>(A.x + B.y, -A.y + B.x);
-    }
+    const int rows_here = (int)max(0LL, min((long long)(2 * PW), rows - 2 * pair0));
+    HalfRows<T, L> half;
+    half.load(reinterpret_cast<const cx<T> *>(a.specB) + 2 * pair0 * KX, rows_here, lane);
+    half.put(tile, lane);
     F::sync();
     cx<T> v[F::V];
     typename F::template TwReg<1> tri;
@@ -495,11 +381,11 @@ __global__ __launch_bounds__(256) void k_x2n(Geo g_in, X2Args a) {
 #pragma unroll
     for (int i = 0; i < F::template nout<1>(); ++i) {
         int p, e;
-        if (!(F::template out_pos<1>(i, p, e) && p < Pact)) continue;
+        if (!F::template out_pos<1>(i, p, e, lane)) continue;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const long long r = 2 * (pair0 + p) + h;
-            if (r >= rows) break;
+            if (2 * p + h >= rows_here) break;
             double n3 = h == 0 ? (double)v[i].x : (double)v[i].y;
             if (a.nref) n3 += (double)ct::cld(a.nref + 3 * N + r * L + e);
             if (!isfinite(n3)) flag |= 5;   // 1: evaluation non-finite, 4: n3 non-finite
@@ -522,17 +408,82 @@ constexpr long long kX2WideBlocks = 384;
 // n3-maximum partial).
 template <typename T, int L, int NODE>
 int launch_x2_form(const Geo &g, const X2Args &a, hipStream_t s) {
-    constexpr int PW = XWide<L>::PW;
+    constexpr int PW = XRow<L>::PW;
     const long long npairs = ((long long)g.ny * g.nz + 1) / 2;
     const long long nw = ct_cdiv(npairs, PW);
-    const bool wide = nw * g.nprob <= kX2WideBlocks;
+    // (eight FP64 values a field leave k_x2h one wave per SIMD with 372 registers: 384 x 96 x 96 345 us
+    // with k_x2w, 319 with k_x2h; the longer rows, with as many, take k_x2w only)
+    constexpr bool only_wide = sizeof(T) == 8 && L > 384;
+    const bool wide = only_wide || nw * g.nprob <= kX2WideBlocks;
     const long long nb = wide ? nw : ct_cdiv(npairs, 2 * PW);
     if (nb > a.red.cap) throw std::runtime_error("x2: reduction buffer too small");
     const dim3 grid((unsigned)nb, 1, (unsigned)g.nprob);
-    if (wide) hipLaunchKernelGGL((k_x2w<T, L, NODE>), grid, dim3(XWide<L>::NTB), 0, s, g, a);
-    else hipLaunchKernelGGL((k_x2h<T, L, NODE>), grid, dim3(256), 0, s, g, a);
+    if (wide) hipLaunchKernelGGL((k_x2w<T, L, NODE>), grid, dim3(kX2WideThreads), 0, s, g, a);
+    else if constexpr (!only_wide) hipLaunchKernelGGL((k_x2h<T, L, NODE>), grid, dim3(256), 0, s, g, a);
     ct_check("x2 (compiled length)");
     return (int)nb;
+}
+
+// Launches the pass; returns the number of blocks (each writes one n3-maximum partial).
+template <typename T, int L>
+int launch_x2_len(const Geo &g, const X2Args &a, hipStream_t s) {
+    constexpr int PW = XRow<L>::PW;
+    const long long npairs = ((long long)g.ny * g.nz + 1) / 2;
+    const bool n3only = a.mode == X2_N3_ONLY;
+    const long long nb = ct_cdiv(npairs, n3only ? 4 * PW : PW);
+    if (nb > a.red.cap) throw std::runtime_error("x2: reduction buffer too small");
+    const dim3 grid((unsigned)nb, 1, (unsigned)g.nprob);
+    if (n3only) {
+        hipLaunchKernelGGL((k_x2n<T, L>), grid, dim3(256), 0, s, g, a);
+    } else if (a.hs != DFT_HS_RSLT) {
+        // other functionals: FP64 nodewise work, kernels of their own (launch_x2_alt_ct)
+        const int nba = launch_x2_alt_ct<T>(g, a, s);
+        if (!nba) throw std::runtime_error("x2: no kernel for this functional");
+        return nba;
+    } else if constexpr (std::is_same<T, float>::value) {
+        // FP32 transforms act on differences from the reference, with FP32 nodewise work
+        if (a.mode != X2_FULL || !a.nref || a.n_out || a.dphi_out || a.nref_out)
+            throw std::runtime_error("x2: FP32 transforms need the reference densities");
+        return launch_x2_form<T, L, X2N_D32>(g, a, s);
+    } else if (a.mode == X2_HESS) {
+        return launch_x2_form<T, L, X2N_HESS>(g, a, s);
+    } else {
+        return launch_x2_form<T, L, X2N_FP64>(g, a, s);
+    }
+    ct_check("x2 (compiled length)");
+    return (int)nb;
+}
+
+template <typename T>
+int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_t s) {
+    switch (g.nx) {
+#define DFT_CASE(n) case n: return launch_x2_len<T, n>(g, a, s);
+        DFT_X_LENGTHS(DFT_CASE)
+#undef DFT_CASE
+        default: return 0;
+    }
+}
+
+// The alternative hard-sphere functionals (Rosenfeld's original vector form, White Bear): FP64
+// nodewise work in kernels of their own, so the kernels of eq. (Phi) keep their register budget.
+template <typename T, int L>
+int launch_x2_alt_len(const Geo &g, const X2Args &a, hipStream_t s) {
+    if constexpr (std::is_same<T, double>::value) {
+        if (a.mode == X2_HESS) return launch_x2_form<T, L, X2N_HESS_ALT>(g, a, s);
+    } else if (a.mode == X2_HESS) {
+        throw std::runtime_error("x2: the Hessian mode has FP64 transforms");
+    }
+    return launch_x2_form<T, L, X2N_ALT>(g, a, s);
+}
+
+template <typename T>
+int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s) {
+    switch (g.nx) {
+#define DFT_CASE(n) case n: return launch_x2_alt_len<T, n>(g, a, s);
+        DFT_X_LENGTHS(DFT_CASE)
+#undef DFT_CASE
+        default: return 0;
+    }
 }
 
 }  // namespace dft

@@ -1,6 +1,8 @@
 // Launchers of the compiled-length y passes (and plain z transforms), with the launch
 // shapes the autotuner chooses among: P adjacent columns per tile (P complex values are
 // contiguous in HBM), threads per tile and one or two LDS exchange buffers.
+#pragma once
+
 #include "ct_kernels.h"
 
 namespace dft {
@@ -27,32 +29,41 @@ constexpr int y_buffers() {
     return (V < 5 && 2 * tile <= kLdsCap) ? 2 : (tile <= kLdsCap ? 1 : 0);
 }
 
+template <typename T, int L, int P, int NTB, int NB>
+bool launch_yc_shape(const Geo &g, const YArgs &a, hipStream_t s) {
+    const bool zax = a.axis == 2;
+    const int ntypes = a.vec == 1 ? 7 : (a.vec == 2 ? 8 : a.nfield);
+    if (zax && a.vec != 0) return false;   // the compact vector layout has y passes only
+    // tiles over the flattened plane of pencils: (y, kx) for the z axis, (z, kx) for the y axis
+    dim3 grid((unsigned)ct_cdiv((zax ? g.ny : g.nz) * g.Kx, P), 1, (unsigned)(ntypes * g.nprob));
+    if (a.vec == 1)
+        hipLaunchKernelGGL((k_yc<T, L, P, NTB, NB, 1>), grid, dim3(NTB), 0, s, g, a);
+    else if (a.vec == 2)
+        hipLaunchKernelGGL((k_yc<T, L, P, NTB, NB, 2>), grid, dim3(NTB), 0, s, g, a);
+    else
+        hipLaunchKernelGGL((k_yc<T, L, P, NTB, NB, 0>), grid, dim3(NTB), 0, s, g, a);
+    ct_check("y (compiled length)");
+    return true;
+}
+
 template <typename T, int L, int V>
-static bool launch_yc_var(const Geo &g, const YArgs &a, hipStream_t s) {
+bool launch_yc_var(const Geo &g, const YArgs &a, hipStream_t s) {
     constexpr int P = y_width<T>(V);
     constexpr int NB = y_buffers<T, L, P, V>();
-    if constexpr (NB == 0) {
-        return false;
-    } else {
-        constexpr int NTB = fit_threads(L, P, y_per_thread(V), 256);
-        const bool zax = a.axis == 2;
-        const int ntypes = a.vec == 1 ? 7 : (a.vec == 2 ? 8 : a.nfield);
-        if (zax && a.vec != 0) return false;   // the compact vector layout has y passes only
-        // tiles over the flattened plane of pencils: (y, kx) for the z axis, (z, kx) for the y axis
-        dim3 grid((unsigned)ct_cdiv((zax ? g.ny : g.nz) * g.Kx, P), 1, (unsigned)(ntypes * g.nprob));
-        if (a.vec == 1)
-            hipLaunchKernelGGL((k_yc<T, L, P, NTB, NB, 1>), grid, dim3(NTB), 0, s, g, a);
-        else if (a.vec == 2)
-            hipLaunchKernelGGL((k_yc<T, L, P, NTB, NB, 2>), grid, dim3(NTB), 0, s, g, a);
-        else
-            hipLaunchKernelGGL((k_yc<T, L, P, NTB, NB, 0>), grid, dim3(NTB), 0, s, g, a);
-        ct_check("y (compiled length)");
-        return true;
-    }
+    if constexpr (NB == 0) return false;
+    else return launch_yc_shape<T, L, P, fit_threads(L, P, y_per_thread(V), 256), NB>(g, a, s);
+}
+
+// The one shape of the lengths outside DFT_CT_LENGTHS: shape 5's columns and LDS buffer.
+template <typename T, int L>
+bool launch_yc_one(const Geo &g, const YArgs &a, hipStream_t s) {
+    constexpr int P = y_width<T>(5), NTB = one_shape_threads<typename ct::PlanT<T, L>::type>(P, 512, 96 / (int)sizeof(T), 64);
+    static_assert(NTB > 0 && L * P * (int)sizeof(cx<T>) <= kLdsCap, "no thread count, or the tile exceeds the LDS");
+    return launch_yc_shape<T, L, P, NTB, 1>(g, a, s);
 }
 
 template <typename T, int L>
-static bool launch_yc_len(const Geo &g, const YArgs &a, hipStream_t s, int v) {
+bool launch_yc_len(const Geo &g, const YArgs &a, hipStream_t s, int v) {
     switch (v) {
         case 1: if (launch_yc_var<T, L, 1>(g, a, s)) return true; break;
         case 2: if (launch_yc_var<T, L, 2>(g, a, s)) return true; break;
@@ -78,22 +89,11 @@ bool launch_y_ct(const Geo &g, const YArgs &a, hipStream_t s) {
 #define DFT_CASE(n) case n: return launch_yc_len<T, n>(g, a, s, v);
         DFT_CT_LENGTHS(DFT_CASE)
 #undef DFT_CASE
+#define DFT_CASE(n) case n: return launch_yc_one<T, n>(g, a, s);
+        DFT_CT_MORE_LENGTHS(DFT_CASE)
+#undef DFT_CASE
         default: return false;
     }
 }
-
-// Number of y shapes for a length (0: no compiled kernel).  A shape whose tile does not
-// fit the LDS runs as shape 0.
-int y_ct_variants(int L, bool) {
-    switch (L) {
-#define DFT_CASE(n) case n: return kYVariants;
-        DFT_CT_LENGTHS(DFT_CASE)
-#undef DFT_CASE
-        default: return 0;
-    }
-}
-
-template bool launch_y_ct<double>(const Geo &, const YArgs &, hipStream_t);
-template bool launch_y_ct<float>(const Geo &, const YArgs &, hipStream_t);
 
 }  // namespace dft

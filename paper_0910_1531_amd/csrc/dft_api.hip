@@ -518,8 +518,10 @@ dft_status dft_setup(const dft_params *params, const double *beta_vext, const do
             g.tab64 = (const double *)(w + lay.tab64);
             launch_spec_tables(g, c->stream);
         }
-        // compact vector layout when every pass of the evaluation runs a compiled-length kernel
-        g.compact = (g.tab64 && x_ct_pairs(g.nx) > 0 && y_ct_variants(g.ny, false) > 0 &&
+        // compact vector layout when every pass of the evaluation runs a compiled-length kernel and
+        // the rows are not the shortest (8 to 18 nodes but for 16)
+        const bool short_rows = g.nx < 24 && g.nx != 16;
+        g.compact = (g.tab64 && x2_ct_min_pairs(g.nx) > 0 && !short_rows && y_ct_variants(g.ny, false) > 0 &&
                      z_ct_variants(g.nz) > 0 && !(g.es && g.cut_lambda)) ? 1 : 0;
         if (!(params->flags & DFT_FLAG_NO_AUTOTUNE)) {
             TuneBufs tb{c->specA, 2 * sizeof(double) * (size_t)g.NC * g.S, c->specB,

@@ -90,11 +90,53 @@ __device__ __forceinline__ void bfly8(cx<T> *v) {
     }
 }
 
+// Radix 6 as 2 x 3 by the coprime map (no inner twiddles): input n = (3 n1 + 2 n2) mod 6, output
+// k = (3 k1 + 4 k2) mod 6.
+template <typename T, int DIR>
+__device__ __forceinline__ void bfly6(cx<T> *v) {
+    cx<T> a[3] = {v[0], v[2], v[4]};   // n1 = 0, n2 = 0, 1, 2
+    cx<T> b[3] = {v[3], v[5], v[1]};   // n1 = 1
+    bfly3<T, DIR>(a);
+    bfly3<T, DIR>(b);
+    v[0] = add(a[0], b[0]);
+    v[3] = sub(a[0], b[0]);
+    v[4] = add(a[1], b[1]);
+    v[1] = sub(a[1], b[1]);
+    v[2] = add(a[2], b[2]);
+    v[5] = sub(a[2], b[2]);
+}
+
+// Radix 9 as 3 x 3: input n = 3 n1 + n2, output k = k1 + 3 k2, inner twiddles exp(DIR 2 pi i n2 k1 / 9).
+template <typename T, int DIR>
+__device__ __forceinline__ void bfly9(cx<T> *v) {
+    const T c1 = T(0.76604444311897803520239265055541668), s1 = T(DIR) * T(0.64278760968653932632264340990726343);
+    const T c2 = T(0.17364817766693034885171662676931480), s2 = T(DIR) * T(0.98480775301220805936674302458952302);
+    const T c4 = T(-0.93969262078590838405410927732473147), s4 = T(DIR) * T(0.34202014332566873304409961468225958);
+    cx<T> a[3] = {v[0], v[3], v[6]}, b[3] = {v[1], v[4], v[7]}, c[3] = {v[2], v[5], v[8]};
+    bfly3<T, DIR>(a);
+    bfly3<T, DIR>(b);
+    bfly3<T, DIR>(c);
+    b[1] = mul(b[1], mk<T>(c1, s1));
+    b[2] = mul(b[2], mk<T>(c2, s2));
+    c[1] = mul(c[1], mk<T>(c2, s2));
+    c[2] = mul(c[2], mk<T>(c4, s4));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        cx<T> u[3] = {a[k], b[k], c[k]};
+        bfly3<T, DIR>(u);
+        v[k] = u[0];
+        v[k + 3] = u[1];
+        v[k + 6] = u[2];
+    }
+}
+
 template <typename T, int DIR, int R>
 __device__ __forceinline__ void bfly(cx<T> *v) {
     if constexpr (R == 2) bfly2<T, DIR>(v);
     else if constexpr (R == 3) bfly3<T, DIR>(v);
     else if constexpr (R == 4) bfly4<T, DIR>(v);
+    else if constexpr (R == 6) bfly6<T, DIR>(v);
+    else if constexpr (R == 9) bfly9<T, DIR>(v);
     else bfly8<T, DIR>(v);
 }
 

@@ -174,7 +174,7 @@ template <typename T> int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_
 template <typename T> int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s);
 template <typename T> bool launch_x1_ct(const Geo &g, const XFwdArgs &a, hipStream_t s);
 template <typename T> bool launch_x3_ct(const Geo &g, const X3Args &a, hipStream_t s);
-int x_ct_pairs(int nx);        // row pairs per block of the compiled-length x kernels, 0 if none
+long long x3_ct_blocks(const Geo &g);   // blocks per field of the compiled-length X3, 0 if none
 int x2_ct_min_pairs(int nx);   // fewest row pairs per block of the length's x2 kernels, 0 if none
 int y_ct_variants(int L, bool fp32);   // launch shapes of the y kernels of length L (0: none)
 int z_ct_variants(int L);              // launch shapes of the z kernels of length L (0: none)

@@ -878,7 +878,7 @@ void launch_z2(const Geo &g, const Z2Args &a, hipStream_t s) {
 template <typename T>
 int x3_nparts(const Geo &g) {
     const long long npairs = ((long long)g.ny * g.nz + 1) / 2;
-    if (const int pb = x_ct_pairs(g.nx)) return (int)ceil_div(npairs, pb) * g.S;
+    if (const long long nb = x3_ct_blocks(g)) return (int)nb * g.S;
     long long P = (NT * Cfg<T>::XE) / g.nx;
     if (P < 1) P = 1;
     if (P > npairs) P = npairs;

@@ -4,7 +4,7 @@
 // radix R has L P / R butterflies spread over the NT threads of the block, and a thread
 // keeps the R values of each of its butterflies in registers.  Between stages the values
 // go through one of two LDS buffers used in turn, so each exchange needs one barrier (a
-// wave-level fence only, where every wave owns whole pencils: see wave_private).
+// wave-level fence only, where every wave owns whole pencils).
 // The first stage takes its inputs from registers that the caller filled (straight from
 // HBM) and the last stage leaves its outputs in registers (stored straight to HBM), so a
 // transform costs (stages - 1) LDS round trips.  The inverse transform runs the radices
@@ -15,8 +15,7 @@
 // With L, P, NT and the radices fixed at compile time every index is a constant or a
 // shift, and the stage loop unrolls completely (no run-time plan, no scratch memory).
 // Twiddles are read from the per-axis table at each stage, or, for blocks that run several
-// transforms in one direction, loaded once into registers (TwReg, or Twiddles for
-// wave-private tiles, which serve both directions).
+// transforms in one direction, loaded once into registers (TwReg).
 #pragma once
 
 #include "dft_device.h"
@@ -98,6 +97,13 @@ constexpr bool xswz_fits(int L) {
         if (xswz<T>(e) >= L) return false;
     return true;
 }
+// The swizzle of a pencil of length L; lengths whose last partial block it would leave keep the
+// elements in order.
+template <typename T, int L>
+__host__ __device__ constexpr int xswz_of(int e) {
+    if constexpr (xswz_fits<T>(L)) return xswz<T>(e);
+    else return e;
+}
 
 // Row swizzle of y and z tiles (pencil index fastest: LDS row e holds element e of the P
 // pencils).  LDS serves 128 bytes per cycle, sixteen 8-byte or eight 16-byte lanes.  Rows of
@@ -106,11 +112,12 @@ constexpr bool xswz_fits(int L) {
 // banks.  XOR-ing higher bits of the row index into its low bit (64-byte rows) or two low
 // bits (32-byte rows) spreads them over distinct banks; the bits are chosen per length by an
 // exhaustive search over this access model (power-of-two lengths: no conflicts left in either
-// direction).  Rows of 128 bytes or more are not swizzled.  A bijection on each aligned
+// direction).  Rows of 128 bytes or more are not swizzled, nor are odd lengths.  A bijection on each aligned
 // block of 2 or 4 rows, so rows stay inside [0, L).
 template <int L, int ROWB>
 __host__ __device__ constexpr int yzswz(int e) {
     constexpr bool pow2 = (L & (L - 1)) == 0;
+    if constexpr (L % 2 != 0) return e;
     const int b2 = (e >> 2) & 1, b3 = (e >> 3) & 1, b4 = (e >> 4) & 1, b5 = (e >> 5) & 1;
     if constexpr (ROWB == 64) {
         if constexpr (pow2 || L == 48) return e ^ (b2 ^ b3);
@@ -149,10 +156,17 @@ constexpr bool yzswz_ok() {
 // wave execute in order, so its reads of one exchange precede its writes of the next.  The
 // caller passes the lane (t, and in place of the buffer phase ph), and may pass it opaque to the
 // compiler so that the index arithmetic of one transform is not kept in registers for another.
-template <typename T, class SC, int P, int NT, bool BF, int NB = 2, int PAD = 0, bool WV = false>
+// OPQ = true: the thread index is opaque at every use, so that arithmetic is redone at every
+// exchange (the LDS positions of swizzled tiles are one register each, and a kernel with many
+// transforms otherwise holds them all throughout).
+template <typename T, class SC, int P, int NT, bool BF, int NB = 2, int PAD = 0, bool WV = false, bool OPQ = false>
 struct Fft {
     static_assert(!WV || (NT == 64 && NB == 1), "a wave's tile has 64 threads and one buffer");
-    __device__ static __forceinline__ int tid() { return WV ? (int)(threadIdx.x & 63) : (int)threadIdx.x; }
+    __device__ static __forceinline__ int tid() {
+        int t = WV ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+        if constexpr (OPQ) asm volatile("" : "+v"(t));
+        return t;
+    }
     static constexpr int L = SC::L;
     static constexpr int NSTG = SC::n;
     static constexpr int LS = BF ? L + PAD : L;
@@ -178,19 +192,8 @@ struct Fft {
         return m;
     }
     static constexpr int V = vmax();   // registers (complex values) per thread
-    // Wave-private tiles: every stage radix 4 with exactly one butterfly per thread, and whole
-    // pencils per wave (L / 4 divides 64).  Each wave then reads and writes only its own pencils'
-    // LDS regions, and the LDS instructions of one wave execute in order, so a wave-level fence
-    // (compiler and memory ordering within the wavefront) replaces the block barrier.
-    static constexpr bool wave_private() {
-        if (!BF || WV) return false;
-        for (int s = 0; s < NSTG; ++s)
-            if (SC::r(s) != 4) return false;
-        return items(4) == NT && NT % 64 == 0 && 64 % (L / 4) == 0;
-    }
-    static constexpr bool WP = wave_private();
     __device__ static __forceinline__ void sync() {
-        if constexpr (WP || WV) {
+        if constexpr (WV) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -214,11 +217,10 @@ struct Fft {
             p = j - b * P;
         }
     }
-    static_assert(!BF || xswz_fits<T>(L), "swizzle leaves the pencil");
     static constexpr int ROWB = P * (int)sizeof(cx<T>);
     static_assert(BF || yzswz_ok<L, ROWB>(), "row swizzle is not a permutation");
     __device__ static __forceinline__ int lidx(int p, int e) {
-        if constexpr (BF) return p * LS + xswz<T>(e);
+        if constexpr (BF) return p * LS + xswz_of<T, L>(e);
         else return yzswz<L, ROWB>(e) * P + p;
     }
 
@@ -265,38 +267,7 @@ struct Fft {
         }
     }
 
-    // In a wave-private tile every stage has radix 4 and one butterfly per thread, so the spans
-    // are 1, 4, 16, ... in either direction and a thread's twiddles are the same for every
-    // transform of the tile (conjugated for the inverse): they can be loaded once into registers.
-    struct Twiddles {
-        cx<T> w[NSTG > 1 ? NSTG - 1 : 1][3];
-    };
-    __device__ static __forceinline__ void load_twiddles(Twiddles &t, const cx<T> *__restrict__ tw) {
-        static_assert(WP, "register twiddles need a wave-private tile");
-        int p, b;
-        decode<4>(tid(), p, b);
-#pragma unroll
-        for (int s = 1; s < NSTG; ++s) {
-            const int NS = 1 << (2 * s);
-            const int k = b % NS, ts = L / (NS * 4);
-#pragma unroll
-            for (int q = 1; q < 4; ++q) t.w[s - 1][q - 1] = cld(tw + q * k * ts);
-        }
-    }
-    template <int DIR, int S>
-    __device__ static __forceinline__ void butterflies_reg(cx<T> *v, const Twiddles &t) {
-        if constexpr (S > 0) {
-#pragma unroll
-            for (int q = 1; q < 4; ++q) {
-                cx<T> w = t.w[S - 1][q - 1];
-                if (DIR > 0) w.y = -w.y;
-                v[q] = mul(v[q], w);
-            }
-        }
-        bfly<T, DIR, 4>(v);
-    }
-
-    // Any tile: the twiddles of all stages of one direction for this thread's butterflies, loaded
+    // The twiddles of all stages of one direction for this thread's butterflies, loaded
     // once (all in flight together) for the transforms of a block that share that direction.
     template <int DIR>
     static constexpr int tw_count(int upto) {
@@ -391,22 +362,6 @@ struct Fft {
         }
     }
 
-    // The same transform with the twiddles from registers (wave-private tiles).
-    template <int DIR, int S = 0>
-    __device__ static __forceinline__ void run(cx<T> *v, cx<T> *lds, int &ph, const Twiddles &t) {
-        constexpr int NS = span<DIR>(S);
-        butterflies_reg<DIR, S>(v, t);
-        if constexpr (S + 1 < NSTG) {
-            cx<T> *buf = lds + (ph ? TILE : 0);
-            ph ^= 1;
-            static_assert(NB == 2, "wave-private tiles alternate two buffers");
-            put<4, NS>(v, buf);
-            sync();
-            get<4>(v, buf);
-            run<DIR, S + 1>(v, lds, ph, t);
-        }
-    }
-
     // Whole transform (unnormalized; DIR = -1 forward, +1 inverse) of the values in v, which
     // hold the first stage's inputs (in_pos) and end holding the outputs (out_pos).  ph is the
     // caller's buffer phase; it must start at 0 and be passed to every call of the block.
@@ -430,18 +385,38 @@ struct Fft {
     }
 };
 
-// Radix schedules of the lengths with compiled kernels (forward order).
+// Radix schedules of the lengths with compiled kernels (forward order).  The z passes end a forward
+// transform holding one butterfly's outputs of every sum, so the last radix is small.
 template <int L> struct Plan;
+template <> struct Plan<8> { using type = Sched<2, 4>; };
+template <> struct Plan<9> { using type = Sched<3, 3>; };
+template <> struct Plan<12> { using type = Sched<3, 4>; };
 template <> struct Plan<16> { using type = Sched<4, 4>; };
+template <> struct Plan<18> { using type = Sched<2, 3, 3>; };
 template <> struct Plan<24> { using type = Sched<8, 3>; };
+template <> struct Plan<27> { using type = Sched<3, 3, 3>; };
 template <> struct Plan<32> { using type = Sched<8, 4>; };
+template <> struct Plan<36> { using type = Sched<3, 3, 4>; };
 template <> struct Plan<48> { using type = Sched<4, 4, 3>; };
+template <> struct Plan<54> { using type = Sched<6, 3, 3>; };
 template <> struct Plan<64> { using type = Sched<8, 8>; };
+template <> struct Plan<72> { using type = Sched<4, 6, 3>; };
+template <> struct Plan<81> { using type = Sched<3, 3, 3, 3>; };
 template <> struct Plan<96> { using type = Sched<8, 4, 3>; };
+template <> struct Plan<108> { using type = Sched<6, 6, 3>; };
 template <> struct Plan<128> { using type = Sched<8, 4, 4>; };
+template <> struct Plan<144> { using type = Sched<8, 6, 3>; };
+template <> struct Plan<162> { using type = Sched<6, 3, 3, 3>; };
 template <> struct Plan<192> { using type = Sched<8, 8, 3>; };
+template <> struct Plan<216> { using type = Sched<6, 4, 3, 3>; };
+template <> struct Plan<243> { using type = Sched<9, 3, 3, 3>; };
 template <> struct Plan<256> { using type = Sched<8, 8, 4>; };
+template <> struct Plan<288> { using type = Sched<8, 4, 3, 3>; };
+template <> struct Plan<324> { using type = Sched<6, 6, 3, 3>; };
 template <> struct Plan<384> { using type = Sched<8, 4, 4, 3>; };
+template <> struct Plan<432> { using type = Sched<8, 6, 3, 3>; };
+template <> struct Plan<486> { using type = Sched<9, 6, 3, 3>; };
+template <> struct Plan<512> { using type = Sched<8, 4, 4, 4>; };
 // Schedule of the y and z transforms in precision T: FP64 tiles hold four values per thread,
 // so at the power-of-two lengths 64, 128 and 256 radix-4 (and one radix-2) stages keep every
 // thread in every stage (a radix-8 stage would leave half of them idle while the other half hold
@@ -451,21 +426,39 @@ template <> struct PlanT<double, 64> { using type = Sched<4, 4, 4>; };
 template <> struct PlanT<double, 128> { using type = Sched<4, 4, 4, 2>; };
 template <> struct PlanT<double, 256> { using type = Sched<4, 4, 4, 4>; };
 
-// Schedules of the x passes: radices of at most 4, the first (forward) being 4 and the
-// last 4 or 2, so a block of L P / 4 threads holds four values of every pencil-element
-// column it owns, the values of several fields at one node stay in one thread, and an
-// inverse transform starts from as many registers as it ends with.
+// Schedules of the x passes.  A wave holds 256 / L pencils (at least one), and radices are small so
+// that its 64 lanes hold about four values each; the first radix (forward) leaves an even number of
+// registers, which the FMT pass splits between two waves.
 template <int L> struct XPlan;
+template <> struct XPlan<8> { using type = Sched<4, 2>; };
+template <> struct XPlan<9> { using type = Sched<3, 3>; };
+template <> struct XPlan<12> { using type = Sched<4, 3>; };
 template <> struct XPlan<16> { using type = Sched<4, 4>; };
+template <> struct XPlan<18> { using type = Sched<2, 3, 3>; };
 template <> struct XPlan<24> { using type = Sched<4, 3, 2>; };
+template <> struct XPlan<27> { using type = Sched<3, 3, 3>; };
 template <> struct XPlan<32> { using type = Sched<4, 4, 2>; };
+template <> struct XPlan<36> { using type = Sched<4, 3, 3>; };
 template <> struct XPlan<48> { using type = Sched<4, 3, 4>; };
+template <> struct XPlan<54> { using type = Sched<6, 3, 3>; };
 template <> struct XPlan<64> { using type = Sched<4, 4, 4>; };
+template <> struct XPlan<72> { using type = Sched<4, 6, 3>; };
+template <> struct XPlan<81> { using type = Sched<3, 3, 3, 3>; };
 template <> struct XPlan<96> { using type = Sched<4, 4, 3, 2>; };
+template <> struct XPlan<108> { using type = Sched<4, 3, 3, 3>; };
 template <> struct XPlan<128> { using type = Sched<4, 4, 4, 2>; };
+template <> struct XPlan<144> { using type = Sched<4, 4, 3, 3>; };
+template <> struct XPlan<162> { using type = Sched<6, 3, 3, 3>; };
 template <> struct XPlan<192> { using type = Sched<4, 4, 3, 4>; };
+template <> struct XPlan<216> { using type = Sched<4, 6, 3, 3>; };
+template <> struct XPlan<243> { using type = Sched<3, 9, 9>; };
 template <> struct XPlan<256> { using type = Sched<4, 4, 4, 4>; };
+template <> struct XPlan<288> { using type = Sched<4, 4, 6, 3>; };
+template <> struct XPlan<324> { using type = Sched<6, 6, 3, 3>; };
 template <> struct XPlan<384> { using type = Sched<4, 4, 4, 3, 2>; };
+template <> struct XPlan<432> { using type = Sched<4, 4, 3, 3, 3>; };
+template <> struct XPlan<486> { using type = Sched<2, 9, 9, 3>; };
+template <> struct XPlan<512> { using type = Sched<8, 8, 8>; };
 
 }  // namespace ct
 }  // namespace dft
