@@ -1329,15 +1329,43 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
         double *inv_den = c->roles.G[(sel + 1) & 3];
         int *hit = reinterpret_cast<int *>(c->roles.G[(sel + 2) & 3]);
         double *raw = c->roles.rho[(sel + 1) & 3];
-        cheb_prep(g.N, rsc, M, cc, dd, inv_den, hit, s);
+        ChebNodes nd;
+        for (int j = 0; j < M; ++j) {
+            const double t = M_PI * (2.0 * j + 1.0) / (2.0 * M);
+            nd.R[j] = cc + dd * std::cos(t);
+            nd.w[j] = (j & 1) ? -std::sin(t) : std::sin(t);
+        }
+        cheb_prep(g.N, rsc, M, nd, inv_den, hit, s);
+        if (ball_ct(g)) {
+            // the fields' full spectra once, then as many radii a pass as specB has slots for
+            YArgs yz{c->specA, g.S, -1, nullptr, 2};
+            launch_y<double>(g, yz, s);
+            BallArgs ba{};
+            ba.specA = c->specA;
+            ba.specB = c->specB;
+            ba.rsc = rsc;
+            ba.inv_den = inv_den;
+            ba.hit = hit;
+            ba.out = f_ref;
+            const int most = std::max(1, kBallSlots / g.S);
+            for (ba.m0 = 0; ba.m0 < M; ba.m0 += ba.nodes) {
+                ba.nodes = std::min(most, M - ba.m0);
+                ba.first = ba.m0 == 0;
+                for (int j = 0; j < ba.nodes; ++j) {
+                    ba.R[j] = nd.R[ba.m0 + j];
+                    ba.w[j] = nd.w[ba.m0 + j];
+                }
+                ball_pass(g, ba, s);
+            }
+            return DFT_OK;
+        }
         for (int m = 0; m < M; ++m) {
-            const double Rm = cc + dd * std::cos(M_PI * (2.0 * m + 1.0) / (2.0 * M));
             Z2Args z2{};
             z2.specA = c->specA;
             z2.specB = c->specB;
             z2.mode = Z2_BALL;
             z2.nsrc = g.S;
-            z2.radius = Rm;
+            z2.radius = nd.R[m];
             launch_z2<double>(g, z2, s);
             YArgs yb{c->specB, g.S, 1, nullptr};
             launch_y<double>(g, yb, s);
@@ -1347,7 +1375,7 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
             x3.raw = 1;
             x3.raw_out = raw;
             launch_x3<double>(g, x3, s);
-            cheb_accum(g.N, g.S, m, M, cc, dd, rsc, inv_den, hit, raw, f_ref, m == 0, s);
+            cheb_accum(g.N, g.S, m, nd, rsc, inv_den, hit, raw, f_ref, m == 0, s);
         }
         return DFT_OK;
     });

@@ -4,8 +4,9 @@
 // point.  Here the ball transform is interpolated in the radius: the field is convolved (by FFT)
 // with the balls of M Chebyshev radii spanning the range of R_SC, and every point combines the M
 // results with the barycentric Lagrange weights of its own radius.  These kernels find the
-// range, the per-point barycentric denominators and do the weighted accumulation; the
-// convolutions run through the transform passes (Z2_BALL).
+// range and the per-point barycentric denominators; the convolutions and the weighted accumulation
+// run several radii a launch on the compiled lengths (ct_screen.h), else one radius at a time through
+// the transform passes (Z2_BALL) and k_cheb_accum.
 #include <stdexcept>
 
 #include "dft_screen.h"
@@ -15,13 +16,6 @@ namespace dft {
 namespace {
 
 constexpr int kNT = 256;
-
-__device__ __forceinline__ void cheb_node(int j, int M, double cc, double dd, double &Rj, double &wj) {
-    double sn, cs;
-    sincospi((2.0 * j + 1.0) / (2.0 * M), &sn, &cs);
-    Rj = cc + dd * cs;
-    wj = (j & 1) ? -sn : sn;
-}
 
 __global__ __launch_bounds__(kNT) void k_rsc_range(long long n, const double *r, double *pmin, double *pmax,
                                                    int *pbad) {
@@ -57,31 +51,27 @@ __global__ __launch_bounds__(kNT) void k_rsc_range(long long n, const double *r,
     }
 }
 
-__global__ __launch_bounds__(kNT) void k_cheb_prep(long long n, const double *r, int M, double cc, double dd,
-                                                   double *inv_den, int *hit) {
+__global__ __launch_bounds__(kNT) void k_cheb_prep(long long n, const double *r, int M, ChebNodes nd, double *inv_den,
+                                                   int *hit) {
     const long long x = (long long)blockIdx.x * kNT + threadIdx.x;
     if (x >= n) return;
     const double R = r[x];
     double den = 0.0;
     int h = -1;
     for (int j = 0; j < M; ++j) {
-        double Rj, wj;
-        cheb_node(j, M, cc, dd, Rj, wj);
-        const double t = R - Rj;
+        const double t = R - nd.R[j];
         if (t == 0.0) h = j;
-        else den += wj / t;
+        else den += nd.w[j] / t;
     }
     inv_den[x] = h >= 0 ? 0.0 : 1.0 / den;
     hit[x] = h;
 }
 
-__global__ __launch_bounds__(kNT) void k_cheb_accum(long long n, int S, int m, int M, double cc, double dd,
+__global__ __launch_bounds__(kNT) void k_cheb_accum(long long n, int S, int m, double Rm, double wm,
                                                     const double *r, const double *inv_den, const int *hit,
                                                     const double *part, double *out, int first) {
     const long long x = (long long)blockIdx.x * kNT + threadIdx.x;
     if (x >= n) return;
-    double Rm, wm;
-    cheb_node(m, M, cc, dd, Rm, wm);
     const int h = hit[x];
     const double l = h >= 0 ? (h == m ? 1.0 : 0.0) : wm / (r[x] - Rm) * inv_den[x];
     for (int i = 0; i < S; ++i) {
@@ -110,15 +100,15 @@ int rsc_range(long long n, const double *r, double *pmin, double *pmax, int *pba
     return (int)nb;
 }
 
-void cheb_prep(long long n, const double *r, int M, double cc, double dd, double *inv_den, int *hit, hipStream_t s) {
-    hipLaunchKernelGGL(k_cheb_prep, dim3((unsigned)blocks_for(n)), dim3(kNT), 0, s, n, r, M, cc, dd, inv_den, hit);
+void cheb_prep(long long n, const double *r, int M, const ChebNodes &nd, double *inv_den, int *hit, hipStream_t s) {
+    hipLaunchKernelGGL(k_cheb_prep, dim3((unsigned)blocks_for(n)), dim3(kNT), 0, s, n, r, M, nd, inv_den, hit);
     check("cheb prep");
 }
 
-void cheb_accum(long long n, int S, int m, int M, double cc, double dd, const double *r, const double *inv_den,
-                const int *hit, const double *part, double *out, bool first, hipStream_t s) {
-    hipLaunchKernelGGL(k_cheb_accum, dim3((unsigned)blocks_for(n)), dim3(kNT), 0, s, n, S, m, M, cc, dd, r, inv_den,
-                       hit, part, out, first ? 1 : 0);
+void cheb_accum(long long n, int S, int m, const ChebNodes &nd, const double *r, const double *inv_den, const int *hit,
+                const double *part, double *out, bool first, hipStream_t s) {
+    hipLaunchKernelGGL(k_cheb_accum, dim3((unsigned)blocks_for(n)), dim3(kNT), 0, s, n, S, m, nd.R[m], nd.w[m], r,
+                       inv_den, hit, part, out, first ? 1 : 0);
     check("cheb accum");
 }
 
