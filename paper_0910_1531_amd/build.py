@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libdftpicard.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
 SOURCES = ["dft_host.cpp", "ct_launch_z1_f32.hip", "ct_launch_y_f32.hip", "ct_launch_y_f64.hip", "ct_launch_z1_f64.hip",
-           "ct_launch_z1_more_f32.hip", "ct_launch_z1_more_f64.hip", "ct_launch_x2_f64.hip", "ct_launch_x2_alt_f64.hip",
+           "ct_launch_zwide_f32.hip", "ct_launch_zwide_f64.hip", "ct_launch_z1_more_f32.hip", "ct_launch_z1_more_f64.hip", "ct_launch_x2_f64.hip", "ct_launch_x2_alt_f64.hip",
            "ct_launch_z2.hip", "ct_launch_x2_f32.hip", "ct_launch_x2_alt_f32.hip", "ct_launch_x.hip", "dft_kernels.hip",
            "ct_launch_screen.hip", "dft_tune.hip", "dft_adjoint.hip", "dft_screen.hip", "dft_api.hip"]
 

@@ -77,6 +77,7 @@ bool launch_z1_more_lengths(const Geo &g, const Z1Args &a, int es, hipStream_t s
 
 template <typename T>
 bool launch_z1_lengths(const Geo &g, const Z1Args &a, int es, hipStream_t s) {
+    if (launch_z1_wide<T>(g, a, es, s)) return true;
     const int v = g.tune[TUNE_Z1][std::is_same<T, float>::value ? 1 : 0];
     switch (g.nz) {
 #define DFT_CASE(n) case n: launch_z1c_len<T, n>(g, a, es, s, v); return true;

@@ -170,6 +170,9 @@ template <typename T> void launch_y(const Geo &g, const YArgs &a, hipStream_t s)
 template <typename T> bool launch_y_ct(const Geo &g, const YArgs &a, hipStream_t s);
 template <typename T> bool launch_z1_ct(const Geo &g, const Z1Args &a, int es, hipStream_t s);
 template <typename T> bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream_t s);
+// Small grids: one wave per transform (ct_zwide.h); false where the rule takes the kernels above.
+template <typename T> bool launch_z1_wide(const Geo &g, const Z1Args &a, int es, hipStream_t s);
+template <typename T> bool launch_z2_wide(const Geo &g, const Z2Args &a, hipStream_t s);
 template <typename T> int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_t s);   // blocks, 0: none
 template <typename T> int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s);
 template <typename T> bool launch_x1_ct(const Geo &g, const XFwdArgs &a, hipStream_t s);

@@ -218,10 +218,12 @@ struct Fft {
         }
     }
     static constexpr int ROWB = P * (int)sizeof(cx<T>);
-    static_assert(BF || yzswz_ok<L, ROWB>(), "row swizzle is not a permutation");
+    // (lengths whose last partial block the row swizzle would leave keep the rows in order)
+    static constexpr bool ROWSWZ = BF || yzswz_ok<L, ROWB>();
     __device__ static __forceinline__ int lidx(int p, int e) {
         if constexpr (BF) return p * LS + xswz_of<T, L>(e);
-        else return yzswz<L, ROWB>(e) * P + p;
+        else if constexpr (ROWSWZ) return yzswz<L, ROWB>(e) * P + p;
+        else return e * P + p;
     }
 
     // Pencil p and element e that register i holds as an input of a first stage (or an
