@@ -136,6 +136,7 @@ __global__ __launch_bounds__(NTB) void k_yc(Geo g_in, YArgs a) {
     const int zc = zax ? 0 : col / Kx;
     const int jx = col - zc * Kx;   // k_x index of the pencil (y axis)
     const int f = (int)blockIdx.z % ntypes;
+    if (f > 0 && n3_wanted(a.n3_only)) return;
     const long long rs = zax ? (long long)g.ny * Kx : (long long)Kx;
     cx<T> *spec = reinterpret_cast<cx<T> *>(a.spec) + (zax ? (long long)col : (long long)zc * g.ny * Kx + jx);
     const cx<T> *tw = twp<T>(g, zax ? 2 : 1);
@@ -509,16 +510,16 @@ __device__ __forceinline__ void z1_species(const Consts &c, const ZWave<T> &kw, 
 template <typename T, class F, int NO>
 __device__ __forceinline__ void z1_inverse(const Geo &g, const Z1Args &a, const ZWave<T> &kw, cx<T> *lds, int &ph,
                                            const cx<T> *tw, int Pact, long long rs, long long off,
-                                           const cx<T> (&acc)[NO][5]) {
+                                           const cx<T> (&acc)[NO][5], bool n3) {
     const Consts &c = *g.cs;
     const long long NC = g.NC;
-    const int ntr = a.n3only ? 1 : 7;
+    const int ntr = n3 ? 1 : 7;
     const T invN = T(c.invN);
     cx<T> v[F::V];
     typename F::template TwReg<1> tri;   // inverse twiddles, shared by the output transforms
     F::template load_tw<1>(tri, tw);
     for (int t = 0; t < ntr; ++t) {
-        const int src = a.n3only ? 3 : (t < 5 ? t : (t == 5 ? 4 : 3));
+        const int src = n3 ? 3 : (t < 5 ? t : (t == 5 ? 4 : 3));
         const bool kzm = t >= 5;
 #pragma unroll
         for (int i = 0; i < NO; ++i) {
@@ -552,7 +553,7 @@ __device__ __forceinline__ void z1_inverse(const Geo &g, const Z1Args &a, const 
                 ct::gst(dst + e * rs + p, w);
             }
         };
-        if (a.n3only) {
+        if (n3) {
             store(0, -1);
         } else if (g.compact) {
             // compact layout: n0..n3, the nV1 sum, nV1_z, nV2_z (the inverse y pass expands)
@@ -596,7 +597,8 @@ __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
     const long long rs = (long long)g.ny * Kx;
     const long long off = zt.off;
     const cx<T> *tw = twp<T>(g, 2);
-    const bool es = MS > 0 && c.es && !a.n3only;
+    const bool n3 = n3_wanted(a.n3_only);
+    const bool es = MS > 0 && c.es && !n3;
     const ZWave<T> kw(c, zt.x, zt.y);
     // the products' constants, read before the first store
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
@@ -666,7 +668,7 @@ __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
                            reinterpret_cast<cx<T> *>(a.specA) + off + ti);
         });
     }
-    z1_inverse<T, F, NO>(g, a, kw, lds, ph, tw, Pact, rs, off, acc);
+    z1_inverse<T, F, NO>(g, a, kw, lds, ph, tw, Pact, rs, off, acc, n3);
 }
 
 // Z1 from z spectra: the same products and inverse transforms as k_z1c, for species spectra
@@ -698,7 +700,8 @@ __global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
     const long long rs = (long long)g.ny * Kx;
     const long long off = zt.off;
     const cx<T> *tw = twp<T>(g, 2);
-    const bool es = MS > 0 && c.es && !a.n3only;
+    const bool n3 = n3_wanted(a.n3_only);
+    const bool es = MS > 0 && c.es && !n3;
     const ZWave<T> kw(c, zt.x, zt.y);
     // the products' constants, read before the first store
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
@@ -742,7 +745,7 @@ __global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
         });
     }
     int ph = 0;
-    z1_inverse<T, F, NO>(g, a, kw, lds, ph, tw, Pact, rs, off, acc);
+    z1_inverse<T, F, NO>(g, a, kw, lds, ph, tw, Pact, rs, off, acc, n3);
 }
 
 // Z2: forward z transform of the ten dPhi/dn spectra, back-convolution with conj(w_hat)

@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
     cx<T> *tile = lds + wave * F::TILE;
     const ZTile zt = z_tile<P>(g);   // (every node of a thread lies in one column)
     const cx<T> *tw = twp<T>(g, 2);
-    const bool es = MS > 0 && c.es && !a.n3only;
+    const bool n3 = n3_wanted(a.n3_only);
+    const bool es = MS > 0 && c.es && !n3;
     const ZWave<T> kw(c, zt.x, zt.y);
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
     constexpr bool TAB = std::is_same<T, double>::value;
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
             z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, true, ti, u, acc,
                            reinterpret_cast<cx<T> *>(a.specA) + zt.off + ti);
         }
-        if (a.n3only) {
+        if (n3) {
             nv[0] = mk<T>(acc[3].x * invN, acc[3].y * invN);
             continue;
         }
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
     }
     __syncthreads();
     const int t = wave;
-    if (t >= (a.n3only ? 1 : 7)) return;
+    if (t >= (n3 ? 1 : 7)) return;
     asm volatile("" : "+v"(lane));
     typename F::template TwReg<1> twi;
     F::template load_tw<1>(twi, tw, lane);
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
             ct::gst(dst + e * rs + p, w);
         }
     };
-    if (a.n3only) {
+    if (n3) {
         store(0, -1);
     } else if (g.compact || t < 3 || t >= 5) {
         store(t < 5 ? t : (t == 5 ? 6 : 9), -1);

@@ -138,6 +138,7 @@ namespace {
 // Options of one residual evaluation.
 struct Eval {
     bool trial = false;            // rho_t = rho0 + alpha (g0 - rho0)
+    bool slot = false;             // the evaluation the state machine has set up (gates and kind from it)
     int kind = -1;                 // >= 0: a line-search pass on the rotating buffers (RoleKind);
                                    // src, g0, rho_t and g_out then come from the roles
     const double *src = nullptr;   // plain: rho; trial: rho0
@@ -165,6 +166,11 @@ void enqueue_eval_t(dft_ctx *c, const Eval &ev, hipStream_t s) {
     const Geo &g = c->geo;
     const bool diff = c->mixed && !ev.fp64;
     const double *rho_eval = ev.trial ? c->rho_t : ev.src;
+    // gates of the passes up to the weighted densities, and of the rest
+    const int *gate = ev.slot ? &c->st->gate_eval : ev.gate;
+    const int *gfull = ev.slot ? &c->st->gate_full : ev.gate;
+    const int *n3_only = ev.slot ? &c->st->n3_only : nullptr;
+    const int *kindp = ev.slot ? &c->st->kind : nullptr;
     XFwdArgs xa{};
     xa.src = ev.src;
     xa.g0 = ev.g0;
@@ -174,21 +180,23 @@ void enqueue_eval_t(dft_ctx *c, const Eval &ev, hipStream_t s) {
     xa.spec = c->specA;
     xa.nfield = g.S;
     xa.mode = ev.trial ? XF_TRIAL : XF_PLAIN;
-    xa.gate = ev.gate;
+    xa.gate = gate;
     if (ev.kind >= 0) {
         xa.roles = c->roles;
         xa.kind = ev.kind;
+        xa.kindp = kindp;
     }
     mark(ev, 0, s);
     launch_x_forward<T>(g, xa, s);
     mark(ev, 1, s);
-    YArgs ya{c->specA, g.S, -1, ev.gate};
+    YArgs ya{c->specA, g.S, -1, gate};
     launch_y<T>(g, ya, s);
     mark(ev, 2, s);
-    Z1Args z1{c->specA, c->specB, 0, diff ? 1 : 0, ev.gate};
+    Z1Args z1{c->specA, c->specB, n3_only, diff ? 1 : 0, gate};
     launch_z1<T>(g, z1, s);
     mark(ev, 3, s);
-    YArgs yb{c->specB, DFT_NALPHA, 1, ev.gate};
+    YArgs yb{c->specB, DFT_NALPHA, 1, gate};
+    yb.n3_only = n3_only;
     yb.vec = g.compact ? 1 : 0;
     launch_y<T>(g, yb, s);
     mark(ev, 4, s);
@@ -201,10 +209,16 @@ void enqueue_eval_t(dft_ctx *c, const Eval &ev, hipStream_t s) {
     x2.n_out = ev.n_out;
     x2.dphi_out = ev.dphi_out;
     x2.red = c->red;
-    x2.gate = ev.gate;
+    x2.gate = gfull;
     const int nb2 = launch_x2<T>(g, x2, s);
+    int nb2n = 0;
+    if (ev.slot) {
+        x2.mode = X2_N3_ONLY;
+        x2.gate = &c->st->gate_n3;
+        nb2n = launch_x2<T>(g, x2, s);
+    }
     mark(ev, 5, s);
-    YArgs yc{c->specB, DFT_NALPHA, -1, ev.gate};
+    YArgs yc{c->specB, DFT_NALPHA, -1, gfull};
     yc.vec = g.compact ? 2 : 0;
     launch_y<T>(g, yc, s);
     mark(ev, 6, s);
@@ -212,10 +226,10 @@ void enqueue_eval_t(dft_ctx *c, const Eval &ev, hipStream_t s) {
     z2.specB = c->specB;
     z2.specA = c->specA;
     z2.mode = Z2_EL;
-    z2.gate = ev.gate;
+    z2.gate = gfull;
     launch_z2<T>(g, z2, s);
     mark(ev, 7, s);
-    YArgs yd{c->specA, g.S, 1, ev.gate};
+    YArgs yd{c->specA, g.S, 1, gfull};
     launch_y<T>(g, yd, s);
     mark(ev, 8, s);
     X3Args x3{};
@@ -229,14 +243,16 @@ void enqueue_eval_t(dft_ctx *c, const Eval &ev, hipStream_t s) {
     x3.e_phi = (ev.e_out && c->p.electrostatics) ? c->phi_fix : nullptr;
     x3.lp_out = ev.refresh ? c->lp : nullptr;
     x3.red = c->red;
-    x3.gate = ev.gate;
+    x3.gate = gfull;
     if (ev.kind >= 0) {
         x3.roles = c->roles;
         x3.kind = ev.kind;
+        x3.kindp = kindp;
     }
     launch_x3<T>(g, x3, s);
     mark(ev, 9, s);
-    launch_finalize(c->red, x3_nparts<T>(g), nb2, ev.fslot, ev.mslot, c->st,
+    if (ev.slot) launch_eval_end(c->red, x3_nparts<T>(g), nb2, nb2n, c->st, s, g.nprob, g.pstride);
+    else launch_finalize(c->red, x3_nparts<T>(g), nb2, ev.fslot, ev.mslot, c->st,
                     ev.count_kind, ev.gate, s, g.nprob, g.pstride);
     mark(ev, 10, s);
 }
@@ -246,76 +262,17 @@ void enqueue_eval(dft_ctx *c, const Eval &ev, hipStream_t s) {
     else enqueue_eval_t<float>(c, ev, s);
 }
 
-// max n3 at rho0 + alpha (g0 - rho0) without the rest of G (linear in rho).
-template <typename T>
-void enqueue_n3_t(dft_ctx *c, const double *alpha, double *mslot, const int *gate, hipStream_t s) {
-    const Geo &g = c->geo;
-    const bool diff = c->mixed;
-    XFwdArgs xa{};
-    xa.alpha = alpha;
-    xa.roles = c->roles;
-    xa.kind = ROLE_N3;
-    xa.ref = diff ? c->rho_ref : nullptr;
-    xa.spec = c->specA;
-    xa.nfield = g.S;
-    xa.mode = XF_TRIAL;
-    xa.gate = gate;
-    launch_x_forward<T>(g, xa, s);
-    YArgs ya{c->specA, g.S, -1, gate};
-    launch_y<T>(g, ya, s);
-    Z1Args z1{c->specA, c->specB, 1, diff ? 1 : 0, gate};
-    launch_z1<T>(g, z1, s);
-    YArgs yb{c->specB, 1, 1, gate};
-    launch_y<T>(g, yb, s);
-    X2Args x2{};
-    x2.specB = c->specB;
-    x2.hs = c->p.hs_functional;
-    x2.mode = X2_N3_ONLY;
-    x2.nref = diff ? c->nref : nullptr;
-    x2.red = c->red;
-    x2.gate = gate;
-    const int nb2 = launch_x2<T>(g, x2, s);
-    launch_finalize(c->red, 0, nb2, nullptr, mslot, c->st, 2, gate, s, g.nprob, g.pstride);
-}
-
-void enqueue_step(dft_ctx *c, hipStream_t s) {
-    DevState *st = c->st;
-    launch_ctl(st, CTL_BEGIN, s, c->geo.nprob, c->geo.pstride);
-    Eval e1;
-    e1.trial = true;
-    e1.kind = ROLE_B;
-    e1.alpha = &st->alpha_trial;
-    e1.fslot = &st->f1;
-    e1.mslot = &st->m1;
-    e1.gate = &st->gate_full1;
-    e1.fp64 = !c->mixed;
-    enqueue_eval(c, e1, s);
-    if (c->mixed) enqueue_n3_t<float>(c, &st->alpha_trial, &st->m1, &st->gate_part1, s);
-    else enqueue_n3_t<double>(c, &st->alpha_trial, &st->m1, &st->gate_part1, s);
-    launch_ctl(st, CTL_AMAX, s, c->geo.nprob, c->geo.pstride);
-    Eval ea = e1;
-    ea.kind = ROLE_A;
-    ea.fslot = &st->fa;
-    ea.mslot = &st->ma;
-    ea.gate = &st->gate_a;
-    enqueue_eval(c, ea, s);
-    launch_ctl(st, CTL_B, s, c->geo.nprob, c->geo.pstride);
-    Eval eb = e1;
-    eb.kind = ROLE_B;
-    eb.fslot = &st->fb;
-    eb.mslot = &st->mb;
-    eb.gate = &st->gate_b;
-    enqueue_eval(c, eb, s);
-    launch_ctl(st, CTL_FIT, s, c->geo.nprob, c->geo.pstride);
-    Eval es = e1;
-    es.kind = ROLE_S;
-    es.fslot = &st->fs;
-    es.mslot = &st->ms;
-    es.gate = &st->gate_s;
-    enqueue_eval(c, es, s);
-    // acceptance rotates the roles: no arrays move
-    launch_ctl(st, CTL_ACCEPT, s, c->geo.nprob, c->geo.pstride);
-    launch_ctl(st, CTL_END, s, c->geo.nprob, c->geo.pstride);
+// One evaluation of the line search, whichever the state machine has set up: its kind, point and
+// gates are device scalars.  An n3-only evaluation (the maximum of n3 at alpha = 1, linear in rho)
+// transforms n3 alone and leaves out the passes after X2.
+void enqueue_slot(dft_ctx *c, hipStream_t s) {
+    Eval e;
+    e.trial = true;
+    e.slot = true;
+    e.kind = ROLE_B;
+    e.alpha = &c->st->alpha_trial;
+    e.fp64 = !c->mixed;
+    enqueue_eval(c, e, s);
 }
 
 // FP64 evaluation at rho0 that also becomes the FP32-mixed reference (or plain prime).
@@ -366,12 +323,15 @@ DevState fresh_state(dft_ctx *c, double tol, long long max_iter) {
     return h;
 }
 
+// A captured graph holds kSlotsPerGraph evaluations.
+constexpr int kSlotsPerGraph = 3;
+
 void ensure_graph(dft_ctx *c) {
     if (c->gexec) return;
     if (!c->cap_stream) HIPCHK(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
     try {
-        enqueue_step(c, c->cap_stream);
+        for (int k = 0; k < kSlotsPerGraph; ++k) enqueue_slot(c, c->cap_stream);
     } catch (...) {
         hipGraph_t tmp;
         (void)hipStreamEndCapture(c->cap_stream, &tmp);
@@ -380,6 +340,32 @@ void ensure_graph(dft_ctx *c) {
     }
     HIPCHK(hipStreamEndCapture(c->cap_stream, &c->graph));
     HIPCHK(hipGraphInstantiate(&c->gexec, c->graph, nullptr, nullptr, 0));
+}
+
+// Evaluations a line search takes: three, where neither the cap nor the packing bound shortens the
+// step, up to four; the host enqueues this many per search left and looks again, so evaluations of
+// searches that needed a fourth cost one more look and no search ends early.
+constexpr int kEvalsPerSearch = 3;
+constexpr int kMaxQueued = 64;   // graphs enqueued between two looks
+
+int graphs_for(int searches) {
+    const long long slots = (long long)searches * kEvalsPerSearch;
+    return (int)std::min<long long>((slots + kSlotsPerGraph - 1) / kSlotsPerGraph, kMaxQueued);
+}
+
+int searches_left(const DevState &h) { return h.phase == PH_IDLE ? 0 : h.steps_left + 1; }
+
+// `steps` line searches (fewer if the problem ends); returns the state after them.
+DevState run_searches(dft_ctx *c, int steps) {
+    launch_ctl(c->st, CTL_BEGIN, c->stream, c->geo.nprob, c->geo.pstride, steps);
+    int n = graphs_for(steps);
+    for (;;) {
+        for (int k = 0; k < n; ++k) HIPCHK(hipGraphLaunch(c->gexec, c->stream));
+        const DevState h = read_state(c);
+        const int left = searches_left(h);
+        if (left == 0) return h;
+        n = graphs_for(left);
+    }
 }
 
 dft_status status_from(const DevState &h) {
@@ -695,8 +681,13 @@ dft_status dft_picard_step(dft_ctx *ctx, double *rho_inout, double *alpha_out, d
         h0.gate_run = 1;
         h0.converged = 0;
         write_state(ctx, h0);
-        enqueue_step(ctx, ctx->stream);
+        launch_ctl(ctx->st, CTL_BEGIN, ctx->stream, 1, 0, 1);
+        for (int k = 0; k < kEvalsPerSearch; ++k) enqueue_slot(ctx, ctx->stream);
         DevState h = read_state(ctx);
+        while (h.phase != PH_IDLE) {
+            enqueue_slot(ctx, ctx->stream);
+            h = read_state(ctx);
+        }
         launch_copy(rho_inout, ctx->roles.rho[h.sel & 3], SN, ctx->stream);
         HIPCHK(hipStreamSynchronize(ctx->stream));
         if (alpha_out) *alpha_out = h.alpha_acc;
@@ -740,8 +731,7 @@ dft_status dft_solve(dft_ctx *ctx, double *rho_inout, double tol, int32_t max_it
                 out = fail(DFT_E_NOT_CONVERGED, "max_iter reached");
                 break;
             }
-            for (int k = 0; k < K; ++k) HIPCHK(hipGraphLaunch(ctx->gexec, ctx->stream));
-            h = read_state(ctx);
+            h = run_searches(ctx, K);
             fp64_checked = !ctx->mixed;
             if (ctx->mixed && !h.converged && !h.status && (h.r < 1e-4 * r_ref || !(h.r < 0.99 * r_prev))) {
                 // refresh the FP64 reference once the residual has fallen far below the
@@ -785,8 +775,7 @@ dft_status dft_run(dft_ctx *ctx, double *rho_inout, int32_t nsteps, int32_t *ite
         h0.converged = 0;
         write_state(ctx, h0);
         ensure_graph(ctx);
-        for (int k = 0; k < nsteps; ++k) HIPCHK(hipGraphLaunch(ctx->gexec, ctx->stream));
-        DevState h = read_state(ctx);
+        DevState h = nsteps > 0 ? run_searches(ctx, nsteps) : h0;
         launch_copy(rho_inout, ctx->roles.rho[h.sel & 3], SN, ctx->stream);
         HIPCHK(hipStreamSynchronize(ctx->stream));
         if (iters_out) *iters_out = (int32_t)(h.iters - it0);
@@ -1645,11 +1634,23 @@ dft_status dft_solve_batch(dft_batch *batch, double *const *rho_inout, double to
                 long long ntot = 0;
                 for (int i : g.idx) ntot += batch->members[i]->geo.N;
                 const int K = ntot >= (1LL << 22) ? 4 : 16;
-                for (int k = 0; k < K; ++k) HIPCHK(hipGraphLaunch(g.lead->gexec, g.stream));
+                launch_ctl(g.lead->st, CTL_BEGIN, g.stream, g.lead->geo.nprob, g.lead->geo.pstride, K);
+                for (int k = 0; k < graphs_for(K); ++k) HIPCHK(hipGraphLaunch(g.lead->gexec, g.stream));
             }
             std::vector<double> r_last(n);
             for (int i = 0; i < n; ++i) r_last[i] = h[i].r;
-            read_all();
+            for (bool idle = false; !idle;) {
+                read_all();
+                idle = true;
+                for (auto &g : batch->groups) {
+                    int left = 0;
+                    for (int i : g.idx) left = std::max(left, searches_left(h[i]));
+                    if (left == 0) continue;
+                    idle = false;
+                    for (int k = 0; k < graphs_for(left); ++k)
+                        HIPCHK(hipGraphLaunch(g.lead->gexec, g.stream));
+                }
+            }
             for (int i = 0; i < n; ++i) {
                 if (done[i]) continue;
                 r_prev[i] = r_last[i];

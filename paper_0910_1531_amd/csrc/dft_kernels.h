@@ -8,6 +8,10 @@
 
 namespace dft {
 
+// The order of a line search's evaluations: alpha = 1 (full, or n3 only while the cap is below 1),
+// amax / 2, amax (unless alpha = 1 was it), the fitted step (unless it is one of these).
+enum EvalPhase { PH_IDLE = 0, PH_ONE = 1, PH_A = 2, PH_B = 3, PH_S = 4 };
+
 // Line-search and status scalars kept in device memory (graph-capturable control).
 struct DevState {
     double f0, m0;          // current iterate: f = ||rho - G(rho)||_w^2, max n3
@@ -17,7 +21,14 @@ struct DevState {
     double r, tol, nfluid, eta_cap;
     double best_f;
     long long iters, rejected, gevals, n3evals, max_iter;
-    int gate_full1, gate_part1, gate_a, gate_b, gate_s, gate_run, gate_one;
+    int gate_run, gate_one;
+    // The evaluation that comes next (advanced by the end of each, k_eval_end)
+    int phase;              // EvalPhase; PH_IDLE: none
+    int kind;               // RoleKind of its x passes
+    int n3_only;            // only the n3 maximum is wanted (ROLE_N3)
+    int gate_eval, gate_full, gate_n3;   // any evaluation; a full one; an n3-only one
+    int full1;              // the evaluation at alpha = 1 was a full one
+    int steps_left;         // line searches still to begin
     int gate_refresh;       // batches: this problem takes the next FP64 reference evaluation
     int src;                // accepted sample: 0 = amax, 1 = amax/2, 2 = vertex
     int status;             // dft_status of the device loop (NONFINITE, PACKING)
@@ -100,6 +111,7 @@ struct XFwdArgs {
     const int *gate;
     Roles roles;              // trial mode with roles.sel: src, g0 and rho_t from the roles (kind)
     int kind;
+    const int *kindp = nullptr;   // device kind, takes the place of kind where set
 };
 
 struct YArgs {
@@ -110,13 +122,14 @@ struct YArgs {
     int axis = 1;       // 1: y, 2: z (plain transform along z)
     int vec = 0;        // compact vector layout of specB (Geo::compact): 1 inverse (7 -> 9 fields),
                         // 2 forward (10 -> 8 fields); 0 plain
+    const int *n3_only = nullptr;   // device flag: transform field 0 only
 };
 
 struct Z1Args {
     void *specA;        // [S] in (after x, y forward); out with electrostatics: the unnormalized
                         // electrostatic spectra sum_j (C_ij - z_i z_j 4 pi l_B / D) rho_hat_j
     void *specB;        // [10] out: n_alpha half spectra after inverse z (x invN)
-    int n3only;         // only n3 into specB[0]
+    const int *n3_only; // device flag: only n3 into specB[0] (null: all)
     int diff;           // FP32-mixed difference evaluation: no bath subtraction
     const int *gate;
 };
@@ -161,6 +174,7 @@ struct X3Args {
     const int *gate;
     Roles roles;              // with roles.sel: rho_t and g_out from the roles (kind)
     int kind;
+    const int *kindp = nullptr;
 };
 
 // Launchers (precision T = double or float of the transforms).
@@ -201,10 +215,15 @@ template <typename T> int x3_nparts(const Geo &g);   // partials written by laun
 // A non-finite evaluation stores +inf in its slots (the line search then rejects it).
 void launch_finalize(const RedBufs &r, int nf, int nm, double *fslot, double *mslot, DevState *st,
                      int count_kind, const int *gate, hipStream_t s, int nprob = 1, long long pstride = 0);
+// End of a line search's evaluation: reduces the partials (nf, nm of a full evaluation, nm_n3 of
+// an n3-only one) and sets up the next evaluation.
+void launch_eval_end(const RedBufs &r, int nf, int nm, int nm_n3, DevState *st, hipStream_t s, int nprob = 1,
+                     long long pstride = 0);
 
-// Control kernels of the line search (one thread per problem of a batch).
-enum CtlOp { CTL_BEGIN = 0, CTL_AMAX = 1, CTL_B = 2, CTL_FIT = 3, CTL_ACCEPT = 4, CTL_END = 5, CTL_PRIME = 6 };
-void launch_ctl(DevState *st, int op, hipStream_t s, int nprob = 1, long long pstride = 0);
+// Control kernels of the line search (one thread per problem of a batch): after a prime
+// evaluation, and the start of `steps` line searches.
+enum CtlOp { CTL_PRIME = 0, CTL_BEGIN = 1 };
+void launch_ctl(DevState *st, int op, hipStream_t s, int nprob = 1, long long pstride = 0, int steps = 0);
 
 // Setup helpers: base_k = mu_k - beta V_k - z_k phi_fixed (-inf where V = +inf), and
 // per-block counts of fluid nodes.

@@ -21,6 +21,7 @@ template <> __device__ __forceinline__ const cx<float> *twp<float>(const Geo &g,
 }
 
 __device__ __forceinline__ bool gated_off(const int *gate) { return gate != nullptr && *gate == 0; }
+__device__ __forceinline__ bool n3_wanted(const int *n3_only) { return n3_only != nullptr && *n3_only != 0; }
 
 // ------------------------------------------------------------------ batches
 // Pointers of problem `prob` of a batch: every workspace pointer moves by prob * pstride.
@@ -45,6 +46,7 @@ __device__ __forceinline__ Roles shift(Roles r, long long o) {
 __device__ __forceinline__ XFwdArgs shift(XFwdArgs a, long long o) {
     a.src = shp(a.src, o); a.g0 = shp(a.g0, o); a.alpha = shp(a.alpha, o); a.rho_t = shp(a.rho_t, o);
     a.ref = shp(a.ref, o); a.spec = shp(a.spec, o); a.gate = shp(a.gate, o); a.roles = shift(a.roles, o);
+    a.kindp = shp(a.kindp, o);
     return a;
 }
 // Entry k of a role table, chosen by selects (a run-time index into the argument array would
@@ -60,21 +62,23 @@ __device__ __forceinline__ int role_sel(const int *sel) { return __builtin_amdgc
 __device__ __forceinline__ void resolve_roles(XFwdArgs &a) {
     if (!a.roles.sel) return;
     const int s = role_sel(a.roles.sel);
+    const int kind = a.kindp ? __builtin_amdgcn_readfirstlane(*a.kindp) : a.kind;
     a.src = role_pick(a.roles.rho, s);
-    if (a.kind == ROLE_PRIME) {
+    if (kind == ROLE_PRIME) {
         a.g0 = role_pick(a.roles.rho, s);
         a.rho_t = nullptr;
     } else {
         a.g0 = role_pick(a.roles.G, s);
-        a.rho_t = a.kind == ROLE_N3 ? nullptr : role_pick(a.roles.rho, (s + 1 + a.kind) & 3);
+        a.rho_t = kind == ROLE_N3 ? nullptr : role_pick(a.roles.rho, (s + 1 + kind) & 3);
     }
 }
 __device__ __forceinline__ YArgs shift(YArgs a, long long o) {
-    a.spec = shp(a.spec, o); a.gate = shp(a.gate, o);
+    a.spec = shp(a.spec, o); a.gate = shp(a.gate, o); a.n3_only = shp(a.n3_only, o);
     return a;
 }
 __device__ __forceinline__ Z1Args shift(Z1Args a, long long o) {
     a.specA = shp(a.specA, o); a.specB = shp(a.specB, o); a.gate = shp(a.gate, o);
+    a.n3_only = shp(a.n3_only, o);
     return a;
 }
 __device__ __forceinline__ Z2Args shift(Z2Args a, long long o) {
@@ -92,12 +96,14 @@ __device__ __forceinline__ X3Args shift(X3Args a, long long o) {
     a.base = shp(a.base, o); a.rho_t = shp(a.rho_t, o); a.g_out = shp(a.g_out, o); a.e_out = shp(a.e_out, o);
     a.e_phi = shp(a.e_phi, o); a.lp_out = shp(a.lp_out, o); a.red = shift(a.red, o); a.gate = shp(a.gate, o);
     a.roles = shift(a.roles, o);
+    a.kindp = shp(a.kindp, o);
     return a;
 }
 __device__ __forceinline__ void resolve_roles(X3Args &a) {
     if (!a.roles.sel) return;
     const int s = role_sel(a.roles.sel);
-    const int t = a.kind == ROLE_PRIME ? s : (s + 1 + a.kind) & 3;
+    const int kind = a.kindp ? __builtin_amdgcn_readfirstlane(*a.kindp) : a.kind;
+    const int t = kind == ROLE_PRIME ? s : (s + 1 + kind) & 3;
     a.rho_t = role_pick(a.roles.rho, t);
     a.g_out = role_pick(a.roles.G, t);
 }
