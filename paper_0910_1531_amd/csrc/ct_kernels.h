@@ -253,6 +253,18 @@ __device__ __forceinline__ ZTile z_tile(const Geo &g) {
     return z;
 }
 
+// Plane of the spectral tables for z element e: the tables are even in k_z and hold z <= L / 2 only, so
+// a tile reads each value twice at close times, the second time from L2.  The z passes are bound by
+// latency and bytes together, and these are 12 rows with three charged species (0.79 of the 2.55 GB of
+// Z1 at 256^3, 0.40 of the 2.3 GB of Z2 when read in full).  Measured us, read in full and halved: 256^3
+// Z1 758 / 709, Z2 791 / 760; 128^3 (two species) 74 / 65, 74 / 68; 108 x 72 x 81 39.5 / 37.3, 39.8 / 38.2.
+// (Pairing the rows y and -y of a plane, to halve them again, breaks lines at the ends of the rows and
+// costs more than it saves: Z1 955, and 30 in the y pass after it.)
+template <int L>
+__device__ __forceinline__ int z_tab(int e) {
+    return e <= L / 2 ? e : L - e;
+}
+
 // Wavenumbers of the elements of one z pencil: column (x, y), z index e.  Only the indices are
 // kept per thread (the grid steps are uniform): the components are formed at each use, which
 // costs a few instructions and no registers across the transforms.
@@ -380,7 +392,7 @@ struct Z1Const {
 };
 
 // Products of one node with electrostatics (S <= MS): the species values u at the node (k_x
-// column p of the tile, z element e; ti its offset in a spectrum, ok whether it is a real
+// column p of the tile, z element e; ti its offset in a spectral table, ok whether it is a real
 // column), the five weighted sums out in acc, and the node's sums over j of K_ij times the
 // species spectra stored at dst + i NC.  Each unordered pair factor is formed once (K_ij = K_ji).
 template <typename T, int MS>
@@ -635,7 +647,7 @@ __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
             for (int i = 0; i < NO; ++i) {
                 int p, e;
                 const bool ok = F::template out_pos<-1>(i, p, e) && p < Pact;
-                z1_species<T>(c, kw, tab, NC, S, jsp, e, ok, ok ? e * rs + p : 0, v[i], acc[i]);
+                z1_species<T>(c, kw, tab, NC, S, jsp, e, ok, ok ? z_tab<L>(e) * rs + p : 0, v[i], acc[i]);
             }
         }
     } else {
@@ -664,7 +676,7 @@ __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
             cx<T> u[MS];
 #pragma unroll
             for (int j = 0; j < MS; ++j) u[j] = us[j][i];
-            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ti, u, acc[i],
+            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i],
                            reinterpret_cast<cx<T> *>(a.specA) + off + ti);
         });
     }
@@ -726,7 +738,7 @@ __global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
             for (int i = 0; i < NO; ++i) {
                 int p, e;
                 const bool ok = F::template in_pos<1>(i, p, e) && p < Pact;
-                z1_species<T>(c, kw, tab, NC, S, jsp, e, ok, ok ? e * rs + p : 0, uin[i], acc[i]);
+                z1_species<T>(c, kw, tab, NC, S, jsp, e, ok, ok ? z_tab<L>(e) * rs + p : 0, uin[i], acc[i]);
             }
         }
     } else {
@@ -741,7 +753,7 @@ __global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
             cx<T> u[MS];
 #pragma unroll
             for (int j = 0; j < MS; ++j) u[j] = (ok && j < S) ? ct::gld(src + (long long)j * NC) : mk<T>(T(0), T(0));
-            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ti, u, acc[i], src);
+            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i], src);
         });
     }
     int ph = 0;
@@ -952,9 +964,11 @@ __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
         for (int i = 0; i < NO; ++i) {
             T w2, w3;
             if constexpr (TAB) {
-                const double *tab = g.tab64 + off;
-                w2 = ct::cld(tab + (long long)is * NC + ti(i));
-                w3 = ct::cld(tab + (long long)(S + is) * NC + ti(i));
+                int p, e;
+                const bool ok = F::template out_pos<-1>(i, p, e) && p < Pact;
+                const double *tab = g.tab64 + off + (ok ? z_tab<L>(e) * rs + p : 0);
+                w2 = ct::cld(tab + (long long)is * NC);
+                w3 = ct::cld(tab + (long long)(S + is) * NC);
             } else {
                 weight_w2_w3<T>(kmag[i], Ri, w2, w3);
             }

@@ -4,7 +4,7 @@
 
 namespace dft {
 
-// Spectral tables (FP64) of the z kernels: one thread per half-spectrum element.
+// Spectral tables (FP64) of the z kernels, z <= n_z / 2 (z_tab): one thread per half-spectrum element.
 __global__ __launch_bounds__(256) void k_spec_tables(Geo g) {
     const long long NC = g.NC;
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -14,6 +14,7 @@ __global__ __launch_bounds__(256) void k_spec_tables(Geo g) {
     const int kx = (int)(i % Kx);
     const long long t = i / Kx;
     const int y = (int)(t % g.ny), e = (int)(t / g.ny);
+    if (2 * e > g.nz) return;   // (even in k_z)
     const ZWave<double> kw(c, kx, y);
     const double kmag = kw.kmag(e);
     double *t64 = const_cast<double *>(g.tab64);

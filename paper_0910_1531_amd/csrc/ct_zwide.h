@@ -79,12 +79,12 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
         if constexpr (MS == 0) {
 #pragma unroll
             for (int m = 0; m < 5; ++m) acc[m] = mk<T>(T(0), T(0));
-            for (int s = 0; s < S; ++s) z1_species<T>(c, kw, tab, NC, S, s, e, true, ti, nv[s * F::TILE], acc);
+            for (int s = 0; s < S; ++s) z1_species<T>(c, kw, tab, NC, S, s, e, true, z_tab<L>(e) * rs + p, nv[s * F::TILE], acc);
         } else {
             cx<T> u[MS];
 #pragma unroll
             for (int s = 0; s < MS; ++s) u[s] = s < S ? nv[s * F::TILE] : mk<T>(T(0), T(0));
-            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, true, ti, u, acc,
+            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, true, z_tab<L>(e) * rs + p, u, acc,
                            reinterpret_cast<cx<T> *>(a.specA) + zt.off + ti);
         }
         if (n3) {
@@ -219,7 +219,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z2w(Geo g_in, Z2Args a) {
             const T Ri = T(c.R[is]), a0 = T(c.i4piR2[is]), a1 = T(c.i4piR[is]);
             T w2, w3;
             if constexpr (std::is_same<T, double>::value) {
-                const double *tab = g.tab64 + zt.off + ti;
+                const double *tab = g.tab64 + zt.off + z_tab<L>(e) * rs + p;
                 w2 = ct::cld(tab + (long long)is * NC);
                 w3 = ct::cld(tab + (long long)(S + is) * NC);
             } else {
