@@ -28,9 +28,12 @@ constexpr int kAdjNV = 4 + 3 * 4 * 4;
 void adj_init(long long n, const double *G, const double *g, double *w, hipStream_t s);
 int adj_r0(long long n, const double *G, const double *Hw, double *r, double *p, double *part, hipStream_t s);
 int adj_q(long long n, const double *G, const double *p, const double *Hp, double *q, double *part, hipStream_t s);
-int adj_step(long long n, double alpha, const double *G, const double *p, const double *q, double *w, double *r,
-             double *part, hipStream_t s);
-void adj_dir(long long n, double beta, const double *G, const double *r, double *p, hipStream_t s);
+// One CG iteration's updates; its scalars stay on the device: rz = r.Gr before, rz_new after the step,
+// pq = p.q.
+int adj_step(long long n, const double *rz, const double *pq, const double *G, const double *p, const double *q,
+             double *w, double *r, double *part, hipStream_t s);
+void adj_dir(long long n, const double *rz_new, const double *rz, const double *G, const double *r, double *p,
+             hipStream_t s);
 int adj_fieldsum(long long N, int S, const double *f, double *part, hipStream_t s);
 void adj_neg(long long n, const double *w, double *out, hipStream_t s);
 void adj_reduce(const double *part, int nparts, int nv, double *out, hipStream_t s);

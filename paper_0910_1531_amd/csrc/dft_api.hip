@@ -1,5 +1,5 @@
 // C ABI of the solver (include/dft.h): context, workspace layout, the residual
-// evaluation sequence, the device-controlled line-search step, HIP graph capture and
+// evaluation sequence, the device-controlled line search, HIP graph capture and
 // the solve loop.
 #include <hip/hip_runtime.h>
 
@@ -933,6 +933,18 @@ Scalars read_scalars(dft_ctx *c, const double *dev, int n) {
     return h;
 }
 
+// One iteration of the conjugate gradients for (diag(G)^-1 - H) w = g: p.q, w and r stepped, the next
+// direction.  cur, nxt: device slots of (r.Gr, r.r) before and after; pq: slot of p.q.
+void enqueue_cg(dft_ctx *c, long long SN, const double *G, const double *nstar, double *w, double *r, double *p,
+                double *q, double *Hp, double *part, const double *cur, double *pq, double *nxt, hipStream_t s) {
+    enqueue_hess(c, p, Hp, nstar, nullptr, s);
+    int nb = adj_q(SN, G, p, Hp, q, part, s);
+    adj_reduce(part, nb, 1, pq, s);
+    nb = adj_step(SN, cur, pq, G, p, q, w, r, part, s);
+    adj_reduce(part, nb, 2, nxt, s);
+    adj_dir(SN, nxt, cur, G, r, p, s);
+}
+
 dft_status adjoint_run(dft_ctx *ctx, const double *rho_star, const double *dO_drho, char *w8, double tol,
                        int32_t max_iter, double *dO_dvext, double *dO_drho_bulk, double *dO_dsigma,
                        int32_t *iters_out, double *resid_out);
@@ -1006,24 +1018,15 @@ dft_status adjoint_run(dft_ctx *ctx, const double *rho_star, const double *dO_dr
         nb = adj_r0(SN, G, Hp, r, p, part, s);
         adj_reduce(part, nb, 2, scal, s);
         Scalars sc = read_scalars(c, scal, 2);
-        double rz = sc[0], rr = sc[1];
         int it = 0;
-        double rel = std::sqrt(rr) / gnorm;
+        double rel = std::sqrt(sc[1]) / gnorm;
         while (rel > tol && it < max_iter) {
-            enqueue_hess(c, p, Hp, nstar, nullptr, s);
-            nb = adj_q(SN, G, p, Hp, q, part, s);
-            adj_reduce(part, nb, 1, scal, s);
-            const double pq = read_scalars(c, scal, 1)[0];
-            if (!(pq > 0.0)) return fail(DFT_E_NONFINITE, "adjoint system is not positive definite at rho*");
-            const double alpha = rz / pq;
-            nb = adj_step(SN, alpha, G, p, q, w, r, part, s);
-            adj_reduce(part, nb, 2, scal, s);
-            sc = read_scalars(c, scal, 2);
-            const double rz_new = sc[0];
-            rr = sc[1];
-            adj_dir(SN, rz_new / rz, G, r, p, s);
-            rz = rz_new;
-            rel = std::sqrt(rr) / gnorm;
+            // scalars: (r.Gr, r.r) in 0-1 and 2-3 by turns, p.q in 4
+            const int nxt = (it & 1) ? 0 : 2;
+            enqueue_cg(c, SN, G, nstar, w, r, p, q, Hp, part, scal + (2 - nxt), scal + 4, scal + nxt, s);
+            sc = read_scalars(c, scal, 5);
+            if (!(sc[4] > 0.0)) return fail(DFT_E_NONFINITE, "adjoint system is not positive definite at rho*");
+            rel = std::sqrt(sc[nxt + 1]) / gnorm;
             ++it;
             if (!std::isfinite(rel)) return fail(DFT_E_NONFINITE, "non-finite adjoint residual");
         }
@@ -1219,20 +1222,13 @@ dft_status dft_newton(dft_ctx *ctx, double *rho, void *adj_ws, size_t adj_ws_byt
                 nb = adj_r0(SN, G, Hp, r, p, part, s);
                 adj_reduce(part, nb, 2, scal, s);
                 Scalars sc = read_scalars(c, scal, 2);
-                double rz = sc[0], rel = std::sqrt(sc[1]) / gnorm;
+                double rel = std::sqrt(sc[1]) / gnorm;
                 for (int k = 0; k < 500 && rel > eta; ++k) {
-                    enqueue_hess(c, p, Hp, nstar, nullptr, s);
-                    nb = adj_q(SN, G, p, Hp, q, part, s);
-                    adj_reduce(part, nb, 1, scal, s);
-                    const double pq = read_scalars(c, scal, 1)[0];
-                    if (!(pq > 0.0)) break;   // not positive definite here: keep the current direction
-                    const double alpha = rz / pq;
-                    nb = adj_step(SN, alpha, G, p, q, d, r, part, s);
-                    adj_reduce(part, nb, 2, scal, s);
-                    sc = read_scalars(c, scal, 2);
-                    adj_dir(SN, sc[0] / rz, G, r, p, s);
-                    rz = sc[0];
-                    rel = std::sqrt(sc[1]) / gnorm;
+                    const int nxt = (k & 1) ? 0 : 2;   // slots as in adjoint_run
+                    enqueue_cg(c, SN, G, nstar, d, r, p, q, Hp, part, scal + (2 - nxt), scal + 4, scal + nxt, s);
+                    sc = read_scalars(c, scal, 5);
+                    if (!(sc[4] > 0.0)) break;   // not positive definite here: keep the current direction
+                    rel = std::sqrt(sc[nxt + 1]) / gnorm;
                     ++cg_total;
                     if (!std::isfinite(rel)) return fail(DFT_E_NONFINITE, "non-finite Newton-Krylov residual");
                 }
@@ -1744,7 +1740,7 @@ dft_status dft_set_schedule(dft_ctx *ctx, const int32_t *shapes) {
     return guarded([&]() -> dft_status {
         for (int p = 0; p < DFT_TUNE_PASSES; ++p)
             for (int t = 0; t < 2; ++t) ctx->geo.tune[p][t] = shapes[2 * p + t];
-        // the captured step graph holds the old launches
+        // the captured graph holds the old launches
         if (ctx->gexec) HIPCHK(hipGraphExecDestroy(ctx->gexec));
         if (ctx->graph) HIPCHK(hipGraphDestroy(ctx->graph));
         ctx->gexec = nullptr;
