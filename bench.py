@@ -43,8 +43,8 @@ def pass_bytes(prob, fp32, compact):
     in the transform precision.  compact: the ten weighted densities leave the z pass as 7
     spectra and reach the x pass as 9, and their derivatives reach the z pass as 8 (the
     context's compact_layout).  FP64 evaluations also read setup-time spectral tables of
-    N_c float64 values per row: the weight spectra w2, w3 of every species in both z passes
-    and, with electrostatics, the S(S+1)/2 pair kernels in the weight pass.
+    N_c float64 values per row, read at z <= nz/2: the weight spectra w2, w3 of every species in
+    both z passes and, with electrostatics, the S(S+1)/2 pair kernels in the weight pass.
     """
     nx, ny, nz = prob.n
     S = prob.nspecies
@@ -55,7 +55,7 @@ def pass_bytes(prob, fp32, compact):
     ref = S * R if fp32 else 0        # FP32-mixed: reference density read in x_fwd
     nref = 10 * 4 * N if fp32 else 0  # FP32-mixed: reference weighted densities read in x_fmt
     zin, xin, zout = (7, 9, 8) if compact else (10, 10, 10)
-    T = 0 if fp32 else 8 * NC         # one FP64 table row
+    T = 0 if fp32 else 8 * (nz // 2 + 1) * ny * (nx // 2 + 1)   # one FP64 table row (even in k_z)
     es = 1 if prob.electrostatics else 0
     return {
         "x_fwd": S * R + ref + S * C,
@@ -195,10 +195,12 @@ def pass_kernel(pass_name, fp32, n, schedule, S):
     if pass_name == "x_el":
         return f"dft::k_x3c<{T}, {n}>"
     if pass_name == "x_fmt":
-        if n in (16, 64, 256):   # paired-wave tiles
-            return f"dft::k_x2p<{T}, {n}>"
-        return f"dft::k_x2c<{T}, {n}, {1 if fp32 else 0}>"
+        if n < 64 or n > 384:   # one wave per field
+            return f"dft::k_x2w<{T}, {n}, {1 if fp32 else 0}>"
+        return f"dft::k_x2h<{T}, {n}, {1 if fp32 else 0}>"
     widths = {0: 8, 1: 4, 2: 16} if fp32 else {0: 4, 1: 2, 2: 8}
+    if n not in (96, 128, 192, 256, 384):
+        return None   # one shape (and small grids: one wave per transform)
     if pass_name == "z_weights":
         v = schedule["z_weights"][1 if fp32 else 0]
         if v >= 3:

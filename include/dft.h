@@ -218,8 +218,8 @@ dft_status dft_picard_step(dft_ctx *ctx, double *rho_inout, double *alpha_out, d
 
 /*
  * Picard iteration until r <= tol or max_iter accepted steps, starting from rho_inout
- * (device [S][N]) and leaving the last iterate there.  The step is a captured HIP graph
- * launched in chunks; the host reads the status between chunks.  In FP32-mixed mode the
+ * (device [S][N]) and leaving the last iterate there.  The line search's evaluations are captured
+ * in a HIP graph launched in chunks of steps; the host reads the status between chunks.  In FP32-mixed mode the
  * FP64 reference is refreshed as the residual falls, and convergence is confirmed with
  * an FP64 evaluation.  iters_out, norm_out: host, may be NULL.
  * Returns DFT_E_NOT_CONVERGED, DFT_E_NONFINITE or DFT_E_PACKING on failure, leaving the
@@ -230,8 +230,8 @@ dft_status dft_solve(dft_ctx *ctx, double *rho_inout, double tol, int32_t max_it
 
 /*
  * Exactly nsteps line-search Picard steps (nonlinear-solver section) on rho_inout
- * (device [S][N]), launched as the captured HIP graph with no convergence stop and one
- * synchronization at the end.  Continues from the previous dft_run / dft_picard_step /
+ * (device [S][N]), launched as the captured HIP graph with no convergence stop; the host waits
+ * where it has queued three evaluations per step, and again for steps that take a fourth.  Continues from the previous dft_run / dft_picard_step /
  * dft_solve state when rho_inout is the buffer those calls last used.  FP32-mixed mode
  * keeps the current reference state (no refresh).  iters_out (accepted steps) and
  * norm_out (r at the last iterate): host, may be NULL.  For benchmarks and for callers
@@ -344,8 +344,8 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
  * Batches of independent state points (different concentrations, valences, radii, grids).
  * Points of one shape (n, nspecies, precision) form a group; every pass of a residual
  * evaluation is ONE launch over all points of a group, the line-search state machines run
- * one device thread per point, and a whole Picard step of a group is one captured HIP
- * graph.  Converged points retire (their work is gated off) while the others continue.
+ * one device thread per point, and the evaluations of a group are launched from one captured HIP
+ * graph (each point at its own place in its line search).  Converged points retire (their work is gated off) while the others continue.
  */
 typedef struct dft_batch dft_batch;
 

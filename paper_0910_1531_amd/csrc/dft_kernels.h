@@ -57,7 +57,8 @@ struct Geo {
     // problems whose workspaces sit pstride bytes apart (blockIdx.z carries the problem).
     int nprob = 1;
     long long pstride = 0;
-    // FP64 spectral tables of the compiled-length z kernels, [row][z][y][kx] (null: none):
+    // FP64 spectral tables of the compiled-length z kernels, [row][z][y][kx] (null: none; even in
+    // k_z, filled for z <= nz / 2):
     // rows 0..S-1 w2_s(k), S..2S-1 w3_s(k), then with electrostatics the
     // screening-minus-Coulomb kernel K_ij(k) of each pair i <= j.
     const double *tab64 = nullptr;
