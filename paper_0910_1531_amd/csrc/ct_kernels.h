@@ -88,11 +88,22 @@ constexpr int z_one_threads(int P) {
 // Measured on 64 x 64 x n_z, three species, us held / redone: FP64 Z1 192 56 / 43, 384 109 / 96,
 // 432 253 / 113, 144 55 / 50, 256 50 / 47 (256^3 788 / 773); Z2 192 71 / 51, 432 209 / 116,
 // 96 28 / 46, 256^3 790 / 823; FP32 Z1 432 107 / 48, 324 67 / 58, 256 38 / 41; Z2 432 133 / 53,
-// 512 69 / 54, 324 58 / 80.
+// 512 69 / 54, 324 58 / 80.  On cubes, two and three species: FP64 Z1 96^3 45 / 37.5, 52 / 43.7, 128^3
+// 65 / 59, 88 / 74; FP32 Z1 (with the waves of z1_waves) 128^3 47 / 41.7, 59 / 47.4, 192^3 108 / 100.6,
+// 143 / 114.5, but 96^3 31.7 / 35.3 and 256^3 338 / 352.
 template <typename T, int L>
 constexpr bool z1_redo() {
-    if (sizeof(T) == 8) return L == 144 || L == 162 || L == 192 || L == 256 || L == 384 || L == 432 || L == 486;
-    return L == 324 || L == 432 || L == 486;
+    if (sizeof(T) == 8) return L == 96 || L == 128 || L == 144 || L == 162 || L == 192 || L == 256 || L == 384 || L == 432 || L == 486;
+    return L == 128 || L == 192 || L == 324 || L == 432 || L == 486;
+}
+// Waves per SIMD Z1's registers are cut to (a few spills against more tiles in flight), by threads per
+// block: the fewest the block needs, but FP32 128 five (96 VGPRs for 102; with four, 128^3 46.7 and 54.5 us
+// where five take 41.7 and 47.4) and 192 four (121 and 138 us left alone, 100.6 and 114.5 with four).
+template <typename T, int L, int NTB>
+constexpr int z1_waves() {
+    if (sizeof(T) == 4 && L == 128) return 5;
+    if (sizeof(T) == 4 && L == 192) return 4;
+    return (NTB + 255) / 256;
 }
 template <typename T, int L>
 constexpr bool z2_redo() {
@@ -586,7 +597,7 @@ __device__ __forceinline__ void z1_inverse(const Geo &g, const Z1Args &a, const 
 }
 
 template <typename T, int L, int P, int NTB, int MS>
-__global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
+__global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, Z1Args a) {
     using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z1_redo<T, L>()>;
     constexpr int NO = F::template nout<-1>();
     static_assert(NO == F::template nin<1>(), "inverse must start where the forward ends");
@@ -690,7 +701,7 @@ __global__ __launch_bounds__(NTB) void k_z1c(Geo g_in, Z1Args a) {
 // starts the inverse transforms from and overwrites them with the electrostatic spectra only
 // after reading them.
 template <typename T, int L, int P, int NTB, int MS>
-__global__ __launch_bounds__(NTB) void k_z1s(Geo g_in, Z1Args a) {
+__global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, Z1Args a) {
     using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z1_redo<T, L>()>;
     constexpr int NO = F::template nin<1>();
     constexpr bool TAB = std::is_same<T, double>::value;
