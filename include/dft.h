@@ -63,8 +63,10 @@ typedef enum dft_status {
 
 typedef enum dft_precision {
     DFT_FP64 = 0,       /* every transform and product in float64 */
-    DFT_FP32_MIXED = 1  /* float32 transforms of differences from an FP64 reference state;
-                           FP64 pointwise FMT, exponent, norms and master density */
+    DFT_FP32_MIXED = 1  /* float32 transforms of differences from an FP64 reference state; FP64
+                           exponent, norms and master density.  dPhi/dn: with n_x = 16, 24, 32, 48, 64,
+                           96, 128, 192, 256 or 384 and DFT_HS_RSLT, float32 differences (log(1 - n3)
+                           and the powers of 1 / (1 - n3) in FP64); otherwise FP64 */
 } dft_precision;
 
 /*

@@ -6,10 +6,24 @@
 
 namespace dft {
 
-// Nodewise variants of X2: FP64 eq. (Phi); FP32 differences from the reference (eq. (Phi),
-// x2_node_diff); FP64 with an alternative functional chosen by X2Args::hs; the product of the
-// FMT Hessian at nstar (X2_HESS) of eq. (Phi) and of an alternative functional.
+// Nodewise variants of X2: FP64 eq. (Phi) (with FP32 transforms, the difference of its values at the density
+// and at the reference, both in FP64); FP32 differences from the reference (eq. (Phi), x2_node_diff); FP64 with
+// an alternative functional chosen by X2Args::hs; the product of the FMT Hessian at nstar (X2_HESS) of eq. (Phi)
+// and of an alternative functional.
 enum X2Node { X2N_FP64 = 0, X2N_D32 = 1, X2N_ALT = 2, X2N_HESS = 3, X2N_HESS_ALT = 4 };
+
+// Rows whose FP32-mixed evaluations form the differences in FP32: the lengths of the tuned kernels (us, FP32
+// differences / FP64: 48^3 13.3 / 14.3, 96^3 39 / 46, 128^3 60 / 86, 256^3 431 / 567).  All other rows take
+// dPhi/dn in FP64, the more precise of the two (the cost there: 27^3 none, 81^3 34 / 50, 108^3 51 / 70, 144^3
+// 113 / 150, 216 x 108 x 108 108 / 140, 512 x 48 x 48 58 / 61).
+constexpr bool x2_fp32_nodes(int L) {
+    switch (L) {
+#define DFT_CASE(n) case n: return true;
+        DFT_CT_LENGTHS(DFT_CASE)
+#undef DFT_CASE
+        default: return false;
+    }
+}
 
 // Small grids.  A block holds PW row pairs and ten waves, one per field: wave f transforms field f of
 // every pair in LDS that only it touches (wave-level fences, no block barrier), then all threads
@@ -441,10 +455,10 @@ int launch_x2_len(const Geo &g, const X2Args &a, hipStream_t s) {
         if (!nba) throw std::runtime_error("x2: no kernel for this functional");
         return nba;
     } else if constexpr (std::is_same<T, float>::value) {
-        // FP32 transforms act on differences from the reference, with FP32 nodewise work
+        // FP32 transforms act on differences from the reference
         if (a.mode != X2_FULL || !a.nref || a.n_out || a.dphi_out || a.nref_out)
             throw std::runtime_error("x2: FP32 transforms need the reference densities");
-        return launch_x2_form<T, L, X2N_D32>(g, a, s);
+        return launch_x2_form<T, L, x2_fp32_nodes(L) ? X2N_D32 : X2N_FP64>(g, a, s);
     } else if (a.mode == X2_HESS) {
         return launch_x2_form<T, L, X2N_HESS>(g, a, s);
     } else {
