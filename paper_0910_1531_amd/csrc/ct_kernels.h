@@ -47,6 +47,26 @@ __device__ __forceinline__ void static_for(Fn &&f) {
     X(8) X(9) X(12) X(18) X(27) X(36) X(54) X(72) X(81) X(108) X(144) X(162) X(216) X(243) X(288) X(324) X(432) X(486) \
     X(512)
 
+constexpr bool tuned_length(int L) {
+    switch (L) {
+#define DFT_CASE(n) case n: return true;
+        DFT_CT_LENGTHS(DFT_CASE)
+#undef DFT_CASE
+        default: return false;
+    }
+}
+
+// Whether the z passes of length L in precision T form wavenumbers in FP64 and round them once, and take the
+// pair factors from the FP64 tables: FP64 at every length, FP32 at the lengths compiled in one shape.  There the
+// FP32 factors formed on the fly were up to three times further from 64 bits than those of the run-time-length
+// kernels before them (pair factors at k R up to 100: 2.0e-7 to 3.4e-7 of their parts, from the tables at most
+// 7.4e-8); the tables cost Z1 time on large grids (three species, us on the fly / tables: 24 x 24 x 162 24.9 / 23.9,
+// 81^3 24.6 / 25.8, 108^3 52 / 61, 144^3 83 / 113, 96 x 96 x 288 90 / 104).  The tuned lengths form theirs on the fly.
+template <typename T, int L>
+constexpr bool z_fp64_factors() {
+    return sizeof(T) == 8 || !tuned_length(L);
+}
+
 // Threads of a tile in the lengths compiled in one shape: of the multiples of 64 up to cap (and of P)
 // that keep at most vcap values per thread in any stage and ocap after the last forward stage, the
 // one that leaves the fewest threads idle over the stages, the larger of equals.
@@ -151,8 +171,9 @@ __global__ __launch_bounds__(NTB) void k_yc(Geo g_in, YArgs a) {
     const long long rs = zax ? (long long)g.ny * Kx : (long long)Kx;
     cx<T> *spec = reinterpret_cast<cx<T> *>(a.spec) + (zax ? (long long)col : (long long)zc * g.ny * Kx + jx);
     const cx<T> *tw = twp<T>(g, zax ? 2 : 1);
-    // grid steps of k_x, k_y read before any store (read later they would be reloaded after each)
-    [[maybe_unused]] const T dkx = T(g.cs->dk[0]), dky = T(g.cs->dk[1]);
+    // grid steps of k_x, k_y read before any store (read later they would be reloaded after each); the
+    // products with the mode are formed in FP64 and rounded once
+    [[maybe_unused]] const double dkx = g.cs->dk[0], dky = g.cs->dk[1];
     cx<T> v[F::V];
     int ph = 0;
     auto body = [&](auto dirc) {
@@ -176,7 +197,7 @@ __global__ __launch_bounds__(NTB) void k_yc(Geo g_in, YArgs a) {
                 if (!(ok && p < Pact)) continue;
                 cx<T> u = w[i];
                 if (mx) {
-                    const T kx = (g.nx % 2 == 0 && 2 * jx == g.nx) ? T(0) : T(jx) * dkx;
+                    const T kx = (g.nx % 2 == 0 && 2 * jx == g.nx) ? T(0) : T(jx * dkx);
                     u = mk<T>(kx * u.y, -kx * u.x);
                 }
                 ct::gst(base + e * rs, u);
@@ -184,7 +205,7 @@ __global__ __launch_bounds__(NTB) void k_yc(Geo g_in, YArgs a) {
         };
         // k_y of element e of the pencil (zero on the Nyquist row)
         auto ky = [&](int e) {
-            return (g.ny % 2 == 0 && 2 * e == g.ny) ? T(0) : T(signed_mode(e, g.ny)) * dky;
+            return (g.ny % 2 == 0 && 2 * e == g.ny) ? T(0) : T(signed_mode(e, g.ny) * dky);
         };
         if constexpr (VEC == 0) {
             load(f, v);
@@ -278,34 +299,36 @@ __device__ __forceinline__ int z_tab(int e) {
 
 // Wavenumbers of the elements of one z pencil: column (x, y), z index e.  Only the indices are
 // kept per thread (the grid steps are uniform): the components are formed at each use, which
-// costs a few instructions and no registers across the transforms.
-template <typename T>
+// costs a few instructions and no registers across the transforms.  U: the type they are formed in.
+template <typename T, typename U = T>
 struct ZWave {
-    T dkx, dky, dkz;
+    U dkx, dky, dkz;
     int x, y, nx, ny, nz;
     __device__ __forceinline__ ZWave(const Consts &c, int x_, int y_) : x(x_), y(y_) {
-        dkx = T(c.dk[0]);
-        dky = T(c.dk[1]);
-        dkz = T(c.dk[2]);
+        dkx = U(c.dk[0]);
+        dky = U(c.dk[1]);
+        dkz = U(c.dk[2]);
         nx = c.nx;
         ny = c.ny;
         nz = c.nz;
     }
-    __device__ __forceinline__ T kx() const { return T(x) * dkx; }
-    __device__ __forceinline__ T ky() const { return T(signed_mode(y, ny)) * dky; }
-    __device__ __forceinline__ T kz(int e) const { return T(signed_mode(e, nz)) * dkz; }
+    __device__ __forceinline__ U kx() const { return U(x) * dkx; }
+    __device__ __forceinline__ U ky() const { return U(signed_mode(y, ny)) * dky; }
+    __device__ __forceinline__ U kz(int e) const { return U(signed_mode(e, nz)) * dkz; }
     __device__ __forceinline__ T kmag(int e) const {
-        const T a = kx(), b = ky(), d = kz(e);
-        return sqrt_r(a * a + b * b + d * d);
+        const U a = kx(), b = ky(), d = kz(e);
+        return T(sqrt_r(a * a + b * b + d * d));
     }
     __device__ __forceinline__ bool zero(int e) const { return x == 0 && y == 0 && e == 0; }
     // component d of k, zero on the Nyquist plane of axis d
     __device__ __forceinline__ T comp(int e, int d) const {
-        if (d == 0) return ((nx % 2 == 0) && 2 * x == nx) ? T(0) : kx();
-        if (d == 1) return ((ny % 2 == 0) && 2 * y == ny) ? T(0) : ky();
-        return ((nz % 2 == 0) && 2 * e == nz) ? T(0) : kz(e);
+        if (d == 0) return ((nx % 2 == 0) && 2 * x == nx) ? T(0) : T(kx());
+        if (d == 1) return ((ny % 2 == 0) && 2 * y == ny) ? T(0) : T(ky());
+        return ((nz % 2 == 0) && 2 * e == nz) ? T(0) : T(kz(e));
     }
 };
+template <typename T, int L>
+using ZWaveOf = ZWave<T, typename std::conditional<z_fp64_factors<T, L>(), double, T>::type>;
 
 // Eigenvalue of minus the 7-point Laplacian, sum_d 4 sin^2(k_d h_d / 2) / h_d^2, from the
 // twiddle tables: k_d h_d = 2 pi j_d / n_d, and tw_d[j] = exp(-2 pi i j / n_d).  The x and y
@@ -340,10 +363,11 @@ __device__ __forceinline__ int pair_row(int S, int i, int j) {
 //       of the exponent sum_j K_ij(k) (rho_hat_j - N rho_b_j delta_k0), K_ij = C_ij(k) -
 //       z_i z_j 4 pi l_B / D(k) (eqs. muESexpansion, potentialSolution), written
 //       unnormalized over rho_hat in specA (z spectral order).
-// FP64 takes the spectral factors from the setup-time tables; FP32 (differences from the
-// reference) evaluates them on the fly: sin and cos of k R once per species, the pair
-// terms by the addition theorem, the Poisson denominator from the twiddle tables -- in
-// FP32 that is cheaper than moving the tables.  The products act on registers between
+// FP64 takes the spectral factors from the setup-time tables.  FP32 (differences from the
+// reference) evaluates them on the fly: sin and cos of k R once per species and, at the tuned
+// lengths, the pair terms by the addition theorem and the Poisson denominator from the twiddle
+// tables, which is cheaper than moving the tables; the other lengths read the pair terms from
+// the tables (z_fp64_factors).  The products act on registers between
 // the forward and inverse transforms.  Every Z1 kernel (fused or split, any tile width) does
 // the same arithmetic in the same order, so the autotuner's choice does not change a result.
 
@@ -406,26 +430,32 @@ struct Z1Const {
 // column p of the tile, z element e; ti its offset in a spectral table, ok whether it is a real
 // column), the five weighted sums out in acc, and the node's sums over j of K_ij times the
 // species spectra stored at dst + i NC.  Each unordered pair factor is formed once (K_ij = K_ji).
-template <typename T, int MS>
-__device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, const ZWave<T> &kw, const Poisson<T> &pd,
+template <bool TAB, typename T, int MS, class ZW>
+__device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, const ZW &kw, const Poisson<T> &pd,
                                         const double *tab, long long NC, int S, bool es, int e, bool ok,
                                         long long ti, const cx<T> (&u)[MS], cx<T> (&acc)[5], cx<T> *dst) {
-    constexpr bool TAB = std::is_same<T, double>::value;
     constexpr int NPR = MS * (MS + 1) / 2;
     T w2[MS], w3[MS], K[NPR];
     // every loop over species or pairs has constant indices (static_for), whatever its size
     if constexpr (TAB) {
         static_for<MS>([&](auto J) __attribute__((always_inline)) {
             constexpr int j = J;
-            w2[j] = (ok && j < S) ? ct::cld(tab + (long long)j * NC + ti) : T(0);
-            w3[j] = (ok && j < S) ? ct::cld(tab + (long long)(S + j) * NC + ti) : T(0);
+            w2[j] = w3[j] = T(0);
+            if constexpr (std::is_same<T, double>::value) {
+                if (ok && j < S) {
+                    w2[j] = ct::cld(tab + (long long)j * NC + ti);
+                    w3[j] = ct::cld(tab + (long long)(S + j) * NC + ti);
+                }
+            } else if (j < S) {
+                weight_w2_w3<T>(kw.kmag(e), k.R[j], w2[j], w3[j]);
+            }
         });
         static_for<MS>([&](auto IA) __attribute__((always_inline)) {
             static_for<MS>([&](auto IB) __attribute__((always_inline)) {
                 constexpr int ia = IA, ib = IB;
                 if constexpr (ib >= ia)
                     K[pair_slot<MS>(ia, ib)] =
-                        (ok && es && ib < S) ? ct::cld(tab + (long long)pair_row(S, ia, ib) * NC + ti) : T(0);
+                        (ok && es && ib < S) ? T(ct::cld(tab + (long long)pair_row(S, ia, ib) * NC + ti)) : T(0);
             });
         });
     } else {
@@ -505,8 +535,8 @@ __device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, cons
 }
 
 // Products of one species at one node without electrostatics (species by species).
-template <typename T>
-__device__ __forceinline__ void z1_species(const Consts &c, const ZWave<T> &kw, const double *tab, long long NC, int S,
+template <typename T, class ZW>
+__device__ __forceinline__ void z1_species(const Consts &c, const ZW &kw, const double *tab, long long NC, int S,
                                            int jsp, int e, bool ok, long long ti, cx<T> u, cx<T> (&acc)[5]) {
     T w2, w3;
     if constexpr (std::is_same<T, double>::value) {
@@ -530,8 +560,8 @@ __device__ __forceinline__ void z1_species(const Consts &c, const ZWave<T> &kw, 
 // are transformed.  Transform t, its source sum and whether it is multiplied by -i k_z:
 //   t = 0..3: acc[t] (n0..n3; t = 3 also gives the x, y components of nV2)
 //   t = 4: acc[4] (x, y components of nV1);  t = 5: -i k_z acc[4] (nV1_z);  t = 6: -i k_z acc[3] (nV2_z)
-template <typename T, class F, int NO>
-__device__ __forceinline__ void z1_inverse(const Geo &g, const Z1Args &a, const ZWave<T> &kw, cx<T> *lds, int &ph,
+template <typename T, class F, int NO, class ZW>
+__device__ __forceinline__ void z1_inverse(const Geo &g, const Z1Args &a, const ZW &kw, cx<T> *lds, int &ph,
                                            const cx<T> *tw, int Pact, long long rs, long long off,
                                            const cx<T> (&acc)[NO][5], bool n3) {
     const Consts &c = *g.cs;
@@ -601,7 +631,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, 
     using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z1_redo<T, L>()>;
     constexpr int NO = F::template nout<-1>();
     static_assert(NO == F::template nin<1>(), "inverse must start where the forward ends");
-    constexpr bool TAB = std::is_same<T, double>::value;
+    constexpr bool TAB = z_fp64_factors<T, L>();
     const int prob = (int)blockIdx.z;
     if (prob > 0) {
         const long long o = (long long)prob * g_in.pstride;
@@ -622,7 +652,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, 
     const cx<T> *tw = twp<T>(g, 2);
     const bool n3 = n3_wanted(a.n3_only);
     const bool es = MS > 0 && c.es && !n3;
-    const ZWave<T> kw(c, zt.x, zt.y);
+    const ZWaveOf<T, L> kw(c, zt.x, zt.y);
     // the products' constants, read before the first store
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
     const double *tab = TAB ? g.tab64 + off : nullptr;
@@ -687,7 +717,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, 
             cx<T> u[MS];
 #pragma unroll
             for (int j = 0; j < MS; ++j) u[j] = us[j][i];
-            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i],
+            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i],
                            reinterpret_cast<cx<T> *>(a.specA) + off + ti);
         });
     }
@@ -704,7 +734,7 @@ template <typename T, int L, int P, int NTB, int MS>
 __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, Z1Args a) {
     using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z1_redo<T, L>()>;
     constexpr int NO = F::template nin<1>();
-    constexpr bool TAB = std::is_same<T, double>::value;
+    constexpr bool TAB = z_fp64_factors<T, L>();
     const int prob = (int)blockIdx.z;
     if (prob > 0) {
         const long long o = (long long)prob * g_in.pstride;
@@ -725,7 +755,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, 
     const cx<T> *tw = twp<T>(g, 2);
     const bool n3 = n3_wanted(a.n3_only);
     const bool es = MS > 0 && c.es && !n3;
-    const ZWave<T> kw(c, zt.x, zt.y);
+    const ZWaveOf<T, L> kw(c, zt.x, zt.y);
     // the products' constants, read before the first store
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
     const double *tab = TAB ? g.tab64 + off : nullptr;
@@ -764,7 +794,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, 
             cx<T> u[MS];
 #pragma unroll
             for (int j = 0; j < MS; ++j) u[j] = (ok && j < S) ? ct::gld(src + (long long)j * NC) : mk<T>(T(0), T(0));
-            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i], src);
+            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i], src);
         });
     }
     int ph = 0;
@@ -775,7 +805,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, 
 // (eq. muHS; the vector parts enter as +i k_d times a w3 weight), plus the electrostatic
 // spectra Z1 left in specA, times 1/N, inverse z -> specA.  Z2_POISSON instead forms the
 // potential of weighted source spectra.
-// Weights: tables in FP64, on the fly in FP32.
+// Weights: tables or on the fly (z_tables).
 template <typename T, int L, int P, int NTB>
 __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
     using F = ct::Fft<T, typename ct::PlanT<T, L>::type, P, NTB, false, 2, 0, false, z2_redo<T, L>()>;
@@ -800,7 +830,7 @@ __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
     const long long rs = (long long)g.ny * Kx;
     const long long off = zt.off;
     const cx<T> *tw = twp<T>(g, 2);
-    const ZWave<T> kw(c, zt.x, zt.y);
+    const ZWaveOf<T, L> kw(c, zt.x, zt.y);
     // position of output register i of the forward transforms (recomputed at each use: a few
     // instructions from the thread index instead of registers held through the kernel)
     auto ee = [&](int i) {

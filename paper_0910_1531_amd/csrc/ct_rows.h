@@ -75,10 +75,10 @@ struct HalfRows {
 
 // Half spectra of the two real rows of every pair from the forward transforms C in the tile; out:
 // first row's half spectrum (the same for all lanes).  times_ikx: both multiplied by i k_x
-// (k_x = k dkx, zero on the Nyquist column).
+// (k_x = k dkx in FP64, rounded once; zero on the Nyquist column).
 template <typename T, int L>
 __device__ __forceinline__ void store_half_rows(const cx<T> *tile, cx<T> *out, int rows_here, int lane, bool times_ikx,
-                                                T dkx) {
+                                                double dkx) {
     using X = XRow<L>;
     using F = typename X::template F<T>;
     constexpr unsigned CB = sizeof(cx<T>);
@@ -92,7 +92,7 @@ __device__ __forceinline__ void store_half_rows(const cx<T> *tile, cx<T> *out, i
         cx<T> a = mk<T>(T(0.5) * (ck.x + cm.x), T(0.5) * (ck.y - cm.y));
         cx<T> b = mk<T>(T(0.5) * (ck.y + cm.y), T(-0.5) * (ck.x - cm.x));
         if (times_ikx) {
-            const T kx = T(k) * dkx;
+            const T kx = T(k * dkx);
             a = mk<T>(-kx * a.y, kx * a.x);
             b = mk<T>(-kx * b.y, kx * b.x);
         }
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void k_x1c(Geo g_in, XFwdArgs a) {
     }
     F::sync();
     store_half_rows<T, L>(tile, reinterpret_cast<cx<T> *>(a.spec) + (long long)f * g.NC + 2 * pair0 * X::KX, rows_here,
-                          lane, false, T(0));
+                          lane, false, 0.0);
 }
 
 // X3: half spectra of E_k (species blockIdx.y) -> inverse x -> Euler-Lagrange update

@@ -62,7 +62,7 @@ k_x2w(Geo g_in, X2Args a) {
     const long long pair0 = (long long)blockIdx.x * PW;
     const int Pact = (int)min((long long)PW, npairs - pair0);
     const cx<T> *tw = twp<T>(g, 0);
-    const T dk0 = T(g.cs->dk[0]);   // k_x step, read before any store
+    const double dk0 = g.cs->dk[0];   // k_x step, read before any store
     // compact layout: n_V2,x = -i k_x n3 is formed here from the n3 spectrum
     const bool from_n3 = g.compact && f == 7;
     // half spectra of the row pairs, every load in flight together
@@ -99,7 +99,7 @@ k_x2w(Geo g_in, X2Args a) {
         for (int i = 0; i < F::template nin<1>(); ++i) {
             int p, e;
             F::template in_pos<1>(i, p, e, lane);
-            const T kx = (L % 2 == 0 && 2 * e == L) ? T(0) : T(e <= L / 2 ? e : e - L) * dk0;
+            const T kx = (L % 2 == 0 && 2 * e == L) ? T(0) : T((e <= L / 2 ? e : e - L) * dk0);
             v[i] = mk<T>(kx * v[i].y, -kx * v[i].x);
         }
     }
@@ -289,7 +289,7 @@ k_x2h(Geo g_in, X2Args a) {
     const long long pair0 = ((long long)blockIdx.x * 2 + (wave >> 1)) * PW;
     const int rows_here = (int)max(0LL, min((long long)(2 * PW), rows - 2 * pair0));   // real rows of the wave
     const cx<T> *tw = twp<T>(g, 0);
-    const T dk0 = T(g.cs->dk[0]);   // k_x step, read before any store
+    const double dk0 = g.cs->dk[0];   // k_x step, read before any store
     HalfRows<T, L> half[5];
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
@@ -311,7 +311,7 @@ k_x2h(Geo g_in, X2Args a) {
             for (int i = 0; i < F::template nin<1>(); ++i) {
                 int p, e;
                 F::template in_pos<1>(i, p, e, lane);
-                const T kx = (X::EVEN && 2 * e == L) ? T(0) : T(e <= L / 2 ? e : e - L) * dk0;
+                const T kx = (X::EVEN && 2 * e == L) ? T(0) : T((e <= L / 2 ? e : e - L) * dk0);
                 v[i] = mk<T>(kx * v3[i].y, -kx * v3[i].x);
             }
         } else {

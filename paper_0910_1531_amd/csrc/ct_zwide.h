@@ -41,9 +41,9 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
     const cx<T> *tw = twp<T>(g, 2);
     const bool n3 = n3_wanted(a.n3_only);
     const bool es = MS > 0 && c.es && !n3;
-    const ZWave<T> kw(c, zt.x, zt.y);
+    const ZWaveOf<T, L> kw(c, zt.x, zt.y);
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
-    constexpr bool TAB = std::is_same<T, double>::value;
+    constexpr bool TAB = z_fp64_factors<T, L>();
     const double *tab = TAB ? g.tab64 + zt.off : nullptr;
     cx<T> v[F::V];
     if (wave < S) {
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
             cx<T> u[MS];
 #pragma unroll
             for (int s = 0; s < MS; ++s) u[s] = s < S ? nv[s * F::TILE] : mk<T>(T(0), T(0));
-            z1_node<T, MS>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, true, z_tab<L>(e) * rs + p, u, acc,
+            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, true, z_tab<L>(e) * rs + p, u, acc,
                            reinterpret_cast<cx<T> *>(a.specA) + zt.off + ti);
         }
         if (n3) {
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z2w(Geo g_in, Z2Args a) {
     cx<T> *tile = lds + t * F::TILE;
     const ZTile zt = z_tile<P>(g);   // (every node of a thread lies in one column)
     const cx<T> *tw = twp<T>(g, 2);
-    const ZWave<T> kw(c, zt.x, zt.y);
+    const ZWaveOf<T, L> kw(c, zt.x, zt.y);
     const cx<T> *specB = reinterpret_cast<const cx<T> *>(a.specB) + zt.off;
     cx<T> v[F::V];
     if (g.compact || t < 4 || t == 5 || t == 7) {
