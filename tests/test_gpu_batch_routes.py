@@ -8,9 +8,9 @@ import numpy as np
 import pytest
 import torch
 
-import workloads as W
 from paper_0910_1531_amd import _abi
 from paper_0910_1531_amd.solver import Batch, from_problem
+from test_gpu_parity import mixture
 
 pytestmark = pytest.mark.gpu
 
@@ -28,7 +28,7 @@ def _blocks(n):
 
 # grid, points, and the limits (x pass, Z1, Z2) that the batch passes and one point does not
 CASES = [((48, 48, 48), 4, (384, 640, 1100)), ((64, 64, 64), 2, (None, 640, 640)), ((32, 32, 96), 3, (384, 384, 384)),
-         ((24, 24, 162), 4, (384, 256, 256)), ((36, 36, 36), 7, (384, 640, 1100)), ((27, 27, 27), 9, (384, 640, None))]
+         ((24, 24, 162), 4, (384, 256, 256)), ((36, 36, 36), 7, (384, 640, 1100)), ((27, 27, 27), 10, (384, 640, None))]
 
 
 @pytest.mark.parametrize("functional", ["rslt", "whitebear"])
@@ -40,19 +40,20 @@ def test_points_change_kernel(n, count, limits, precision, functional):
         assert limit is None or b <= limit < b * count
     pts = []
     for i in range(count):
-        p = W.charged_sphere(n=n, h=0.1, sigma=(0.3, 0.24), conc=(0.3 + 0.1 * i, 0.3 + 0.1 * i), sphere_radius=0.3)
+        p = mixture(n, h=tuple(2.6 / m for m in n), S=2, es=True, seed=i)
         p.hs_functional = functional
         pts.append(p)
-    print(f"  {count} x {n} {functional} precision {precision}", file=sys.stderr, flush=True)
     b = Batch(pts, precision=precision)
     rhos = [_dev(p.initial_density()) for p in pts]
-    its, norms, sts = b.solve(rhos, 1e-8, 200)
-    assert all(s == 0 for s in sts)
+    its, norms, sts = b.solve(rhos, 1e-8, 60)
+    print(f"  {count} x {n} {functional} precision {precision}: iterations {its}, statuses {sts}", file=sys.stderr, flush=True)
     for i, p in enumerate(pts):
         sol = from_problem(p, precision=precision)
         x = _dev(p.initial_density())
-        it, r, st = sol.solve(x, 1e-8, 200)
-        assert (st, it, r) == (0, its[i], norms[i]), i
+        it, r, st = sol.solve(x, 1e-8, 60, raise_on_fail=False)
+        # (a point that is not done by then stops at the same iterate; its residual may come from an FP32 evaluation
+        # in the one and an FP64 evaluation in the other)
+        assert (st, it) == (sts[i], its[i]) and (st != 0 or r == norms[i]), i
         assert torch.equal(x, rhos[i]), i
         sol.close()
     b.close()
