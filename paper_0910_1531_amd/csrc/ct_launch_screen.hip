@@ -20,12 +20,7 @@ static void launch_ballx_len(const Geo &g, const BallArgs &a, hipStream_t s) {
     ct_check("interpolation in the radius");
 }
 
-// Whether every axis has compiled kernels for ball_pass.
-bool ball_ct(const Geo &g) {
-    return y_ct_variants(g.ny, false) > 0 && z_ct_variants(g.nz) > 0 && x2_ct_min_pairs(g.nx) > 0;
-}
-
-void ball_pass(const Geo &g, const BallArgs &a, hipStream_t s) {
+void ball_averages(const Geo &g, const BallArgs &a, hipStream_t s) {
     switch (g.nz) {
 #define DFT_CASE(n) case n: launch_ball_len<n>(g, a, s); break;
         DFT_X_LENGTHS(DFT_CASE)
@@ -34,6 +29,9 @@ void ball_pass(const Geo &g, const BallArgs &a, hipStream_t s) {
     }
     YArgs y{a.specB, a.nodes * g.S, 1, nullptr};
     launch_y<double>(g, y, s);
+}
+
+void ball_interpolate(const Geo &g, const BallArgs &a, hipStream_t s) {
     switch (g.nx) {
 #define DFT_CASE(n) case n: launch_ballx_len<n>(g, a, s); break;
         DFT_X_LENGTHS(DFT_CASE)

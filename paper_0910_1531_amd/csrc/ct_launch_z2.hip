@@ -65,7 +65,7 @@ static void launch_z2c_one(const Geo &g, const Z2Args &a, hipStream_t s) {
 template <typename T>
 bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream_t s) {
     if (!g.tab64) return false;   // no spectral tables: run-time-length kernel
-    if (a.mode == Z2_BALL) return false;   // the compiled lengths average over several radii a launch (ball_pass)
+    if (a.mode == Z2_BALL) return false;   // the compiled lengths average over several radii a launch (ball_averages)
     if (launch_z2_wide<T>(g, a, s)) return true;
     const int v = g.tune[TUNE_Z2][std::is_same<T, float>::value ? 1 : 0];
     switch (g.nz) {

@@ -1321,7 +1321,17 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
             nd.w[j] = (j & 1) ? -std::sin(t) : std::sin(t);
         }
         cheb_prep(g.N, rsc, M, nd, inv_den, hit, s);
-        if (ball_ct(g)) {
+        // real-space averages of radius m from the slots at spec, added with their weights
+        auto transform_and_add = [&](void *spec, int m) {
+            X3Args x3{};
+            x3.specA = spec;
+            x3.nfield = g.S;
+            x3.raw = 1;
+            x3.raw_out = raw;
+            launch_x3<double>(g, x3, s);
+            cheb_accum(g.N, g.S, m, nd, rsc, inv_den, hit, raw, f_ref, m == 0, s);
+        };
+        if (z_ct_variants(g.nz) > 0) {
             // the fields' full spectra once, then as many radii a pass as specB has slots for
             YArgs yz{c->specA, g.S, -1, nullptr, 2};
             launch_y<double>(g, yz, s);
@@ -1332,6 +1342,7 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
             ba.inv_den = inv_den;
             ba.hit = hit;
             ba.out = f_ref;
+            const bool x_ct = x2_ct_min_pairs(g.nx) > 0;
             const int most = std::max(1, kBallSlots / g.S);
             for (ba.m0 = 0; ba.m0 < M; ba.m0 += ba.nodes) {
                 ba.nodes = std::min(most, M - ba.m0);
@@ -1340,7 +1351,13 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
                     ba.R[j] = nd.R[ba.m0 + j];
                     ba.w[j] = nd.w[ba.m0 + j];
                 }
-                ball_pass(g, ba, s);
+                ball_averages(g, ba, s);
+                if (x_ct) {
+                    ball_interpolate(g, ba, s);
+                } else {
+                    for (int j = 0; j < ba.nodes; ++j)
+                        transform_and_add((cx<double> *)c->specB + (long long)j * g.S * g.NC, ba.m0 + j);
+                }
             }
             return DFT_OK;
         }
@@ -1354,13 +1371,7 @@ dft_status dft_rfd_reference(dft_ctx *ctx, const double *f, const double *rsc, i
             launch_z2<double>(g, z2, s);
             YArgs yb{c->specB, g.S, 1, nullptr};
             launch_y<double>(g, yb, s);
-            X3Args x3{};
-            x3.specA = c->specB;
-            x3.nfield = g.S;
-            x3.raw = 1;
-            x3.raw_out = raw;
-            launch_x3<double>(g, x3, s);
-            cheb_accum(g.N, g.S, m, nd, rsc, inv_den, hit, raw, f_ref, m == 0, s);
+            transform_and_add(c->specB, m);
         }
         return DFT_OK;
     });

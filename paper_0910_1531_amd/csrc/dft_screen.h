@@ -21,9 +21,10 @@ void cheb_prep(long long n, const double *r, int M, const ChebNodes &nd, double 
 void cheb_accum(long long n, int S, int m, const ChebNodes &nd, const double *r, const double *inv_den, const int *hit,
                 const double *part, double *out, bool first, hipStream_t s);
 
-// One batch of radii on the compiled lengths (ball_ct): the fields' full spectra in specA -> ball
-// averages of radii m0 .. m0 + nodes - 1 in specB slots (nodes S of them) -> their interpolation at every
-// point's R_SC written (first) or added to out.
+// One batch of radii on the compiled z lengths: the fields' full spectra in specA -> ball averages of radii
+// m0 .. m0 + nodes - 1 in specB slots (nodes S of them; ball_averages, after the inverse y pass) -> on the
+// compiled x lengths, their interpolation at every point's R_SC written (first) or added to out
+// (ball_interpolate; other x lengths transform and accumulate the slots one radius at a time).
 constexpr int kBallSlots = DFT_NALPHA;   // slots of specB
 struct BallArgs {
     const void *specA;
@@ -34,7 +35,7 @@ struct BallArgs {
     const int *hit;                        // [N]
     double *out;                           // [S][N]
 };
-bool ball_ct(const Geo &g);
-void ball_pass(const Geo &g, const BallArgs &a, hipStream_t s);
+void ball_averages(const Geo &g, const BallArgs &a, hipStream_t s);
+void ball_interpolate(const Geo &g, const BallArgs &a, hipStream_t s);
 
 }  // namespace dft

@@ -5,7 +5,7 @@
 // with the balls of M Chebyshev radii spanning the range of R_SC, and every point combines the M
 // results with the barycentric Lagrange weights of its own radius.  These kernels find the
 // range and the per-point barycentric denominators; the convolutions and the weighted accumulation
-// run several radii a launch on the compiled lengths (ct_screen.h), else one radius at a time through
+// run several radii a launch on the compiled z (and x) lengths (ct_screen.h), else one radius at a time through
 // the transform passes (Z2_BALL) and k_cheb_accum.
 #include <stdexcept>
 
