@@ -17,9 +17,21 @@ LIB = os.path.join(HERE, "libdftpicard.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 
 SOURCES = ["dft_host.cpp", "ct_launch_z1_f32.hip", "ct_launch_y_f32.hip", "ct_launch_y_f64.hip", "ct_launch_z1_f64.hip",
-           "ct_launch_zwide_f32.hip", "ct_launch_zwide_f64.hip", "ct_launch_z1_more_f32.hip", "ct_launch_z1_more_f64.hip", "ct_launch_x2_f64.hip", "ct_launch_x2_alt_f64.hip",
-           "ct_launch_z2.hip", "ct_launch_x2_f32.hip", "ct_launch_x2_alt_f32.hip", "ct_launch_x.hip", "dft_kernels.hip",
-           "ct_launch_screen.hip", "dft_tune.hip", "dft_adjoint.hip", "dft_screen.hip", "dft_api.hip"]
+           "ct_launch_zwide_f32.hip", "ct_launch_zwide_f64.hip", "ct_launch_z1_more_f32.hip", "ct_launch_z1_more_f64.hip",
+           "ct_launch_z2.hip", "ct_launch_x.hip", "dft_kernels.hip", "ct_launch_screen.hip", "dft_tune.hip", "dft_adjoint.hip",
+           "dft_screen.hip", "dft_api.hip"]
+# The X2 kernels: one code object per precision, class (the Hessian product in FP64 only) and group of row lengths.
+X2_CLASSES = {"double": range(4), "float": (0, 2)}
+X2_GROUPS = 6
+
+
+def units():
+    """(object name, source, macro definitions) of every translation unit, the longest to compile first."""
+    out = [(os.path.splitext(s)[0], s, []) for s in SOURCES]
+    out += [(f"ct_launch_x2_{t}_{c}_{g}", "ct_launch_x2.hip", [f"-DDFT_X2_T={t}", f"-DDFT_X2_CLASS={c}", f"-DDFT_X2_GROUP={g}"])
+            for t, classes in X2_CLASSES.items() for c in classes for g in range(X2_GROUPS)]
+    return out
+
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -28,14 +40,17 @@ DEVICE = ["--offload-arch=" + ARCH, "-Xclang", "-target-feature", "-Xclang", "-p
           "-munsafe-fp-atomics", "-ffp-contract=on"]
 
 
-def _compile(src):
+def _compile(unit):
+    name, src, defs = unit
     path = os.path.join(CSRC, src)
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
+    cwd = os.path.join(BUILD, name)   # each unit's own folder: the files hipcc keeps are named after the source
+    os.makedirs(cwd, exist_ok=True)
+    obj = os.path.join(cwd, name + ".o")
     if src.endswith(".hip"):
-        cmd = [HIPCC, "-x", "hip"] + DEVICE + COMMON + ["-save-temps=obj", "-c", path, "-o", obj]
+        cmd = [HIPCC, "-x", "hip"] + DEVICE + COMMON + defs + ["-save-temps=obj", "-c", path, "-o", obj]
     else:
         cmd = [HIPCC, "-x", "c++"] + COMMON + ["-c", path, "-o", obj]
-    r = subprocess.run(cmd, cwd=BUILD, capture_output=True, text=True)
+    r = subprocess.run(cmd, cwd=cwd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
     return obj, r.stderr
@@ -44,8 +59,8 @@ def _compile(src):
 def build(verbose=False):
     """Compile every source and link the shared library; returns its path."""
     os.makedirs(BUILD, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 8)) as ex:
-        results = list(ex.map(_compile, SOURCES))
+    with concurrent.futures.ThreadPoolExecutor(max_workers=os.cpu_count() or 8) as ex:
+        results = list(ex.map(_compile, units()))
     objs = [o for o, _ in results]
     if verbose:
         for (o, err) in results:

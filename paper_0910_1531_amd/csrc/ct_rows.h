@@ -8,7 +8,17 @@
 
 namespace dft {
 
-#define DFT_X_LENGTHS(X) DFT_CT_LENGTHS(X) DFT_CT_MORE_LENGTHS(X)
+// Row lengths, in groups: the X2 kernels of a group are a code object of their own (ct_launch_x2.hip), since the
+// runtime loads a whole code object at the first launch from it (about 1.3 ms per MB).
+#define DFT_X_GROUP_0(X) X(8) X(9) X(12) X(16) X(18)
+#define DFT_X_GROUP_1(X) X(24) X(27) X(32) X(36) X(48)
+#define DFT_X_GROUP_2(X) X(54) X(64) X(72) X(81) X(96)
+#define DFT_X_GROUP_3(X) X(108) X(128) X(144) X(162) X(192)
+#define DFT_X_GROUP_4(X) X(216) X(243) X(256) X(288) X(324)
+#define DFT_X_GROUP_5(X) X(384) X(432) X(486) X(512)
+constexpr int kXGroups = 6;
+#define DFT_X_LENGTHS(X) \
+    DFT_X_GROUP_0(X) DFT_X_GROUP_1(X) DFT_X_GROUP_2(X) DFT_X_GROUP_3(X) DFT_X_GROUP_4(X) DFT_X_GROUP_5(X)
 
 // Element at a 32-bit byte offset of a base that all lanes share: the base stays in scalar registers
 // and a lane holds one register of address.

@@ -438,66 +438,27 @@ int launch_x2_form(const Geo &g, const X2Args &a, hipStream_t s) {
     return (int)nb;
 }
 
-// Launches the pass; returns the number of blocks (each writes one n3-maximum partial).
+// n3 only; returns the number of blocks (each writes one n3-maximum partial).
 template <typename T, int L>
-int launch_x2_len(const Geo &g, const X2Args &a, hipStream_t s) {
-    constexpr int PW = XRow<L>::PW;
-    const long long npairs = ((long long)g.ny * g.nz + 1) / 2;
-    const bool n3only = a.mode == X2_N3_ONLY;
-    const long long nb = ct_cdiv(npairs, n3only ? 4 * PW : PW);
+int launch_x2n_len(const Geo &g, const X2Args &a, hipStream_t s) {
+    const long long nb = ct_cdiv(((long long)g.ny * g.nz + 1) / 2, 4 * XRow<L>::PW);
     if (nb > a.red.cap) throw std::runtime_error("x2: reduction buffer too small");
-    const dim3 grid((unsigned)nb, 1, (unsigned)g.nprob);
-    if (n3only) {
-        hipLaunchKernelGGL((k_x2n<T, L>), grid, dim3(256), 0, s, g, a);
-    } else if (a.hs != DFT_HS_RSLT) {
-        // other functionals: FP64 nodewise work, kernels of their own (launch_x2_alt_ct)
-        const int nba = launch_x2_alt_ct<T>(g, a, s);
-        if (!nba) throw std::runtime_error("x2: no kernel for this functional");
-        return nba;
-    } else if constexpr (std::is_same<T, float>::value) {
-        // FP32 transforms act on differences from the reference
-        if (a.mode != X2_FULL || !a.nref || a.n_out || a.dphi_out || a.nref_out)
-            throw std::runtime_error("x2: FP32 transforms need the reference densities");
-        return launch_x2_form<T, L, x2_fp32_nodes(L) ? X2N_D32 : X2N_FP64>(g, a, s);
-    } else if (a.mode == X2_HESS) {
-        return launch_x2_form<T, L, X2N_HESS>(g, a, s);
-    } else {
-        return launch_x2_form<T, L, X2N_FP64>(g, a, s);
-    }
-    ct_check("x2 (compiled length)");
+    hipLaunchKernelGGL((k_x2n<T, L>), dim3((unsigned)nb, 1, (unsigned)g.nprob), dim3(256), 0, s, g, a);
+    ct_check("x2 (n3 only)");
     return (int)nb;
 }
 
-template <typename T>
-int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_t s) {
-    switch (g.nx) {
-#define DFT_CASE(n) case n: return launch_x2_len<T, n>(g, a, s);
-        DFT_X_LENGTHS(DFT_CASE)
-#undef DFT_CASE
-        default: return 0;
-    }
-}
-
-// The alternative hard-sphere functionals (Rosenfeld's original vector form, White Bear): FP64
-// nodewise work in kernels of their own, so the kernels of eq. (Phi) keep their register budget.
-template <typename T, int L>
-int launch_x2_alt_len(const Geo &g, const X2Args &a, hipStream_t s) {
-    if constexpr (std::is_same<T, double>::value) {
-        if (a.mode == X2_HESS) return launch_x2_form<T, L, X2N_HESS_ALT>(g, a, s);
-    } else if (a.mode == X2_HESS) {
-        throw std::runtime_error("x2: the Hessian mode has FP64 transforms");
-    }
-    return launch_x2_form<T, L, X2N_ALT>(g, a, s);
-}
-
-template <typename T>
-int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s) {
-    switch (g.nx) {
-#define DFT_CASE(n) case n: return launch_x2_alt_len<T, n>(g, a, s);
-        DFT_X_LENGTHS(DFT_CASE)
-#undef DFT_CASE
-        default: return 0;
-    }
+// The pass of one class and row length.  The classes but the first are kernels of their own, so the kernels of
+// eq. (Phi) keep their register budget: the Hessian product (FP64 transforms) and the alternative hard-sphere
+// functionals (Rosenfeld's original vector form, White Bear; FP64 nodewise work).
+template <typename T, int CLASS, int L>
+int launch_x2_len(const Geo &g, const X2Args &a, hipStream_t s) {
+    if constexpr (CLASS == X2C_HESS) return launch_x2_form<T, L, X2N_HESS>(g, a, s);
+    else if constexpr (CLASS == X2C_ALT) return launch_x2_form<T, L, X2N_ALT>(g, a, s);
+    else if constexpr (CLASS == X2C_HESS_ALT) return launch_x2_form<T, L, X2N_HESS_ALT>(g, a, s);
+    else if (a.mode == X2_N3_ONLY) return launch_x2n_len<T, L>(g, a, s);
+    // FP32 transforms act on differences from the reference
+    else return launch_x2_form<T, L, std::is_same<T, float>::value && x2_fp32_nodes(L) ? X2N_D32 : X2N_FP64>(g, a, s);
 }
 
 }  // namespace dft

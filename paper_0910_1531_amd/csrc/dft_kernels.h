@@ -189,7 +189,10 @@ template <typename T> bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream
 template <typename T> bool launch_z1_wide(const Geo &g, const Z1Args &a, int es, hipStream_t s);
 template <typename T> bool launch_z2_wide(const Geo &g, const Z2Args &a, hipStream_t s);
 template <typename T> int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_t s);   // blocks, 0: none
-template <typename T> int launch_x2_alt_ct(const Geo &g, const X2Args &a, hipStream_t s);
+// One class of X2 launches in one group of compiled row lengths (ct_launch_x2.hip): eq. (Phi) and the n3-only
+// mode, the Hessian product, and the same of the alternative functionals.
+enum X2Class { X2C_PLAIN = 0, X2C_HESS = 1, X2C_ALT = 2, X2C_HESS_ALT = 3 };
+template <typename T, int CLASS, int GROUP> int launch_x2_unit(const Geo &g, const X2Args &a, hipStream_t s);
 template <typename T> bool launch_x1_ct(const Geo &g, const XFwdArgs &a, hipStream_t s);
 template <typename T> bool launch_x3_ct(const Geo &g, const X3Args &a, hipStream_t s);
 long long x3_ct_blocks(const Geo &g);   // blocks per field of the compiled-length X3, 0 if none
