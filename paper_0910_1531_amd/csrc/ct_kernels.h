@@ -131,6 +131,15 @@ constexpr bool z2_redo() {
     return L == 432 || L == 486 || L == 512;
 }
 
+// Grid step of k_x or k_y in the compact layout's x and y passes.  T(mode * step) is the FP64 wavenumber
+// rounded once, or with Geo::fp64_k off the FP32 product of the mode and the rounded step (that product is
+// exact in FP64).
+template <typename T>
+__device__ __forceinline__ double k_step(const Geo &g, int axis) {
+    const double dk = axis == 0 ? g.cs->dk[0] : g.cs->dk[1];
+    return std::is_same<T, double>::value || g.fp64_k ? dk : (double)(T)dk;
+}
+
 // ------------------------------------------------------------------ y / z plain transforms
 // One block transforms P adjacent pencils of one field along y or z; the pencils' elements sit
 // rs apart in HBM, and adjacent pencils of one row are adjacent in HBM.
@@ -171,9 +180,8 @@ __global__ __launch_bounds__(NTB) void k_yc(Geo g_in, YArgs a) {
     const long long rs = zax ? (long long)g.ny * Kx : (long long)Kx;
     cx<T> *spec = reinterpret_cast<cx<T> *>(a.spec) + (zax ? (long long)col : (long long)zc * g.ny * Kx + jx);
     const cx<T> *tw = twp<T>(g, zax ? 2 : 1);
-    // grid steps of k_x, k_y read before any store (read later they would be reloaded after each); the
-    // products with the mode are formed in FP64 and rounded once
-    [[maybe_unused]] const double dkx = g.cs->dk[0], dky = g.cs->dk[1];
+    // grid steps of k_x, k_y read before any store (read later they would be reloaded after each)
+    [[maybe_unused]] const double dkx = k_step<T>(g, 0), dky = k_step<T>(g, 1);
     cx<T> v[F::V];
     int ph = 0;
     auto body = [&](auto dirc) {

@@ -85,7 +85,7 @@ struct HalfRows {
 
 // Half spectra of the two real rows of every pair from the forward transforms C in the tile; out:
 // first row's half spectrum (the same for all lanes).  times_ikx: both multiplied by i k_x
-// (k_x = k dkx in FP64, rounded once; zero on the Nyquist column).
+// (k_x = k dkx, rounded once; zero on the Nyquist column).
 template <typename T, int L>
 __device__ __forceinline__ void store_half_rows(const cx<T> *tile, cx<T> *out, int rows_here, int lane, bool times_ikx,
                                                 double dkx) {

@@ -62,7 +62,7 @@ k_x2w(Geo g_in, X2Args a) {
     const long long pair0 = (long long)blockIdx.x * PW;
     const int Pact = (int)min((long long)PW, npairs - pair0);
     const cx<T> *tw = twp<T>(g, 0);
-    const double dk0 = g.cs->dk[0];   // k_x step, read before any store
+    const double dk0 = k_step<T>(g, 0);   // k_x step, read before any store
     // compact layout: n_V2,x = -i k_x n3 is formed here from the n3 spectrum
     const bool from_n3 = g.compact && f == 7;
     // half spectra of the row pairs, every load in flight together
@@ -289,7 +289,7 @@ k_x2h(Geo g_in, X2Args a) {
     const long long pair0 = ((long long)blockIdx.x * 2 + (wave >> 1)) * PW;
     const int rows_here = (int)max(0LL, min((long long)(2 * PW), rows - 2 * pair0));   // real rows of the wave
     const cx<T> *tw = twp<T>(g, 0);
-    const double dk0 = g.cs->dk[0];   // k_x step, read before any store
+    const double dk0 = k_step<T>(g, 0);   // k_x step, read before any store
     HalfRows<T, L> half[5];
 #pragma unroll
     for (int j = 0; j < 5; ++j) {

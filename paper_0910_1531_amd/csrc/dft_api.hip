@@ -509,6 +509,7 @@ dft_status dft_setup(const dft_params *params, const double *beta_vext, const do
         const bool short_rows = g.nx < 24 && g.nx != 16;
         g.compact = (g.tab64 && x2_ct_min_pairs(g.nx) > 0 && !short_rows && y_ct_variants(g.ny, false) > 0 &&
                      z_ct_variants(g.nz) > 0 && !(g.es && g.cut_lambda)) ? 1 : 0;
+        g.fp64_k = z_ct_variants(g.nz) == 1 ? 1 : 0;
         if (!(params->flags & DFT_FLAG_NO_AUTOTUNE)) {
             TuneBufs tb{c->specA, 2 * sizeof(double) * (size_t)g.NC * g.S, c->specB,
                         2 * sizeof(double) * (size_t)g.NC * DFT_NALPHA};

@@ -52,6 +52,9 @@ struct Geo {
     // multiplies the x components of the derivatives by i k_x, the forward y pass folds the y
     // components in (slots 0-4, 6, 7, 9) and Z2 reads those.
     int compact = 0;
+    // FP32 wavenumbers of the compact layout's x and y passes rounded once from FP64 (n_z outside the tuned
+    // lengths), as in the z passes (z_fp64_factors); else from FP32 grid steps.
+    int fp64_k = 0;
     long long N, NC;
     // Batches of identically shaped problems: the kernels of one launch cover nprob
     // problems whose workspaces sit pstride bytes apart (blockIdx.z carries the problem).
