@@ -438,6 +438,9 @@ int launch_x2_form(const Geo &g, const X2Args &a, hipStream_t s) {
     return (int)nb;
 }
 
+// Longest rows of the Hessian product: dft_adjoint and dft_newton refuse longer ones before any launch.
+constexpr int kX2HessMax = 384;
+
 // n3 only; returns the number of blocks (each writes one n3-maximum partial).
 template <typename T, int L>
 int launch_x2n_len(const Geo &g, const X2Args &a, hipStream_t s) {
@@ -453,7 +456,9 @@ int launch_x2n_len(const Geo &g, const X2Args &a, hipStream_t s) {
 // functionals (Rosenfeld's original vector form, White Bear; FP64 nodewise work).
 template <typename T, int CLASS, int L>
 int launch_x2_len(const Geo &g, const X2Args &a, hipStream_t s) {
-    if constexpr (CLASS == X2C_HESS) return launch_x2_form<T, L, X2N_HESS>(g, a, s);
+    if constexpr ((CLASS == X2C_HESS || CLASS == X2C_HESS_ALT) && L > kX2HessMax) {
+        throw std::runtime_error("x2: the Hessian mode needs n_x <= 384");
+    } else if constexpr (CLASS == X2C_HESS) return launch_x2_form<T, L, X2N_HESS>(g, a, s);
     else if constexpr (CLASS == X2C_ALT) return launch_x2_form<T, L, X2N_ALT>(g, a, s);
     else if constexpr (CLASS == X2C_HESS_ALT) return launch_x2_form<T, L, X2N_HESS_ALT>(g, a, s);
     else if (a.mode == X2_N3_ONLY) return launch_x2n_len<T, L>(g, a, s);
