@@ -299,6 +299,26 @@ bool launch_z2w_len(const Geo &g, const Z2Args &a, hipStream_t s) {
     }
 }
 
+// Whether Z1 (Z2) of the grid takes the kernels here, whatever the tuned shape.
+template <typename T>
+bool z1_is_wide(const Geo &g) {
+    switch (g.nz) {
+#define DFT_CASE(n) case n: return z_wide<T, n, false>(g);
+        DFT_ZWIDE_LENGTHS(DFT_CASE)
+#undef DFT_CASE
+        default: return false;
+    }
+}
+template <typename T>
+bool z2_is_wide(const Geo &g) {
+    switch (g.nz) {
+#define DFT_CASE(n) case n: return z_wide<T, n, true>(g);
+        DFT_ZWIDE_LENGTHS(DFT_CASE)
+#undef DFT_CASE
+        default: return false;
+    }
+}
+
 // False where the rule takes the kernels with one block per tile, or the length has no kernel here.
 template <typename T>
 bool launch_z1_wide(const Geo &g, const Z1Args &a, int es, hipStream_t s) {

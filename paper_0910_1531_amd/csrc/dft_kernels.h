@@ -191,6 +191,8 @@ template <typename T> bool launch_z2_ct(const Geo &g, const Z2Args &a, hipStream
 // Small grids: one wave per transform (ct_zwide.h); false where the rule takes the kernels above.
 template <typename T> bool launch_z1_wide(const Geo &g, const Z1Args &a, int es, hipStream_t s);
 template <typename T> bool launch_z2_wide(const Geo &g, const Z2Args &a, hipStream_t s);
+template <typename T> bool z1_is_wide(const Geo &g);   // the rule alone: the tuned shapes have no effect
+template <typename T> bool z2_is_wide(const Geo &g);
 template <typename T> int launch_x2_ct(const Geo &g, const X2Args &a, hipStream_t s);   // blocks, 0: none
 // One class of X2 launches in one group of compiled row lengths (ct_launch_x2.hip): eq. (Phi) and the n3-only
 // mode, the Hessian product, and the same of the alternative functionals.

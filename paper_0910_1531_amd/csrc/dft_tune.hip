@@ -29,14 +29,17 @@ using Key = std::tuple<int, int, int, int, int, int, int, int>;   // pass, fp32,
 std::map<Key, int> g_cache;
 std::mutex g_mu;
 
+// Launch shapes to choose among.  Small grids run the z passes' weights and back-convolution in kernels without
+// shapes (z1_is_wide, z2_is_wide): nothing to time.
+template <typename T>
 int variants_of(const Geo &g, int pass) {
     switch (pass) {
         case TUNE_Y:
         case TUNE_YF:
         case TUNE_YS: return g.ny > 1 ? y_ct_variants(g.ny, false) : 0;
         case TUNE_YZ: return g.nz > 1 ? y_ct_variants(g.nz, false) : 0;
-        case TUNE_Z1: return z1_ct_variants(g.nz);
-        default: return z_ct_variants(g.nz);
+        case TUNE_Z1: return z1_is_wide<T>(g) ? 1 : z1_ct_variants(g.nz);
+        default: return z2_is_wide<T>(g) ? 1 : z_ct_variants(g.nz);
     }
 }
 
@@ -127,7 +130,7 @@ template <typename T>
 void tune_precision(Geo &g, const TuneBufs &b, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const int t = sizeof(T) == 4 ? 1 : 0;
     for (int pass = 0; pass < DFT_TUNE_PASSES; ++pass) {
-        const int nv = variants_of(g, pass);
+        const int nv = variants_of<T>(g, pass);
         g.tune[pass][t] = 0;
         if (nv <= 1) continue;
         const Key key{pass, t, g.nx, g.ny, g.nz, g.S, g.es, g.nprob};
