@@ -305,6 +305,12 @@ __device__ __forceinline__ int z_tab(int e) {
     return e <= L / 2 ? e : L - e;
 }
 
+// Elements of a row of the tables (rs = n_y Kx, a z plane).
+template <int L>
+__device__ __forceinline__ long long z_tab_row(long long rs) {
+    return (L / 2 + 1) * rs;
+}
+
 // Wavenumbers of the elements of one z pencil: column (x, y), z index e.  Only the indices are
 // kept per thread (the grid steps are uniform): the components are formed at each use, which
 // costs a few instructions and no registers across the transforms.  U: the type they are formed in.
@@ -358,7 +364,7 @@ struct Poisson {
     }
 };
 
-// Pair row of the spectral table (rows [row][z][y][kx], see Geo::tab64): K_ij, i <= j.
+// Pair row of the spectral tables (Geo::tab64): K_ij, i <= j.
 __device__ __forceinline__ int pair_row(int S, int i, int j) {
     const int a = min(i, j), b = max(i, j);
     return 2 * S + a * S - (a * (a - 1)) / 2 + (b - a);
@@ -435,12 +441,12 @@ struct Z1Const {
 };
 
 // Products of one node with electrostatics (S <= MS): the species values u at the node (k_x
-// column p of the tile, z element e; ti its offset in a spectral table, ok whether it is a real
+// column p of the tile, z element e; ti its offset in a row of TS elements of the spectral tables, ok whether it is a real
 // column), the five weighted sums out in acc, and the node's sums over j of K_ij times the
 // species spectra stored at dst + i NC.  Each unordered pair factor is formed once (K_ij = K_ji).
 template <bool TAB, typename T, int MS, class ZW>
 __device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, const ZW &kw, const Poisson<T> &pd,
-                                        const double *tab, long long NC, int S, bool es, int e, bool ok,
+                                        const double *tab, long long TS, long long NC, int S, bool es, int e, bool ok,
                                         long long ti, const cx<T> (&u)[MS], cx<T> (&acc)[5], cx<T> *dst) {
     constexpr int NPR = MS * (MS + 1) / 2;
     T w2[MS], w3[MS], K[NPR];
@@ -451,8 +457,8 @@ __device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, cons
             w2[j] = w3[j] = T(0);
             if constexpr (std::is_same<T, double>::value) {
                 if (ok && j < S) {
-                    w2[j] = ct::cld(tab + (long long)j * NC + ti);
-                    w3[j] = ct::cld(tab + (long long)(S + j) * NC + ti);
+                    w2[j] = ct::cld(tab + (long long)j * TS + ti);
+                    w3[j] = ct::cld(tab + (long long)(S + j) * TS + ti);
                 }
             } else if (j < S) {
                 weight_w2_w3<T>(kw.kmag(e), k.R[j], w2[j], w3[j]);
@@ -463,7 +469,7 @@ __device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, cons
                 constexpr int ia = IA, ib = IB;
                 if constexpr (ib >= ia)
                     K[pair_slot<MS>(ia, ib)] =
-                        (ok && es && ib < S) ? T(ct::cld(tab + (long long)pair_row(S, ia, ib) * NC + ti)) : T(0);
+                        (ok && es && ib < S) ? T(ct::cld(tab + (long long)pair_row(S, ia, ib) * TS + ti)) : T(0);
             });
         });
     } else {
@@ -544,12 +550,12 @@ __device__ __forceinline__ void z1_node(const Z1Const<T, MS> &k, bool diff, cons
 
 // Products of one species at one node without electrostatics (species by species).
 template <typename T, class ZW>
-__device__ __forceinline__ void z1_species(const Consts &c, const ZW &kw, const double *tab, long long NC, int S,
+__device__ __forceinline__ void z1_species(const Consts &c, const ZW &kw, const double *tab, long long TS, int S,
                                            int jsp, int e, bool ok, long long ti, cx<T> u, cx<T> (&acc)[5]) {
     T w2, w3;
     if constexpr (std::is_same<T, double>::value) {
-        w2 = ok ? ct::cld(tab + (long long)jsp * NC + ti) : T(0);
-        w3 = ok ? ct::cld(tab + (long long)(S + jsp) * NC + ti) : T(0);
+        w2 = ok ? ct::cld(tab + (long long)jsp * TS + ti) : T(0);
+        w3 = ok ? ct::cld(tab + (long long)(S + jsp) * TS + ti) : T(0);
     } else {
         weight_w2_w3<T>(kw.kmag(e), T(c.R[jsp]), w2, w3);
     }
@@ -664,6 +670,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, 
     // the products' constants, read before the first store
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
     const double *tab = TAB ? g.tab64 + off : nullptr;
+    [[maybe_unused]] const long long TS = z_tab_row<L>(rs);
     cx<T> acc[NO][5];
     cx<T> v[F::V];
     int ph = 0;
@@ -696,7 +703,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, 
             for (int i = 0; i < NO; ++i) {
                 int p, e;
                 const bool ok = F::template out_pos<-1>(i, p, e) && p < Pact;
-                z1_species<T>(c, kw, tab, NC, S, jsp, e, ok, ok ? z_tab<L>(e) * rs + p : 0, v[i], acc[i]);
+                z1_species<T>(c, kw, tab, TS, S, jsp, e, ok, ok ? z_tab<L>(e) * rs + p : 0, v[i], acc[i]);
             }
         }
     } else {
@@ -725,7 +732,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1c(Geo g_in, 
             cx<T> u[MS];
 #pragma unroll
             for (int j = 0; j < MS; ++j) u[j] = us[j][i];
-            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i],
+            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, TS, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i],
                            reinterpret_cast<cx<T> *>(a.specA) + off + ti);
         });
     }
@@ -767,6 +774,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, 
     // the products' constants, read before the first store
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
     const double *tab = TAB ? g.tab64 + off : nullptr;
+    [[maybe_unused]] const long long TS = z_tab_row<L>(rs);
     cx<T> acc[NO][5];
     if constexpr (MS == 0) {
         // species by species, every node's input of a species in flight together
@@ -787,7 +795,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, 
             for (int i = 0; i < NO; ++i) {
                 int p, e;
                 const bool ok = F::template in_pos<1>(i, p, e) && p < Pact;
-                z1_species<T>(c, kw, tab, NC, S, jsp, e, ok, ok ? z_tab<L>(e) * rs + p : 0, uin[i], acc[i]);
+                z1_species<T>(c, kw, tab, TS, S, jsp, e, ok, ok ? z_tab<L>(e) * rs + p : 0, uin[i], acc[i]);
             }
         }
     } else {
@@ -802,7 +810,7 @@ __global__ __launch_bounds__(NTB, (z1_waves<T, L, NTB>())) void k_z1s(Geo g_in, 
             cx<T> u[MS];
 #pragma unroll
             for (int j = 0; j < MS; ++j) u[j] = (ok && j < S) ? ct::gld(src + (long long)j * NC) : mk<T>(T(0), T(0));
-            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i], src);
+            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, TS, NC, S, es, e, ok, ok ? z_tab<L>(e) * rs + p : 0, u, acc[i], src);
         });
     }
     int ph = 0;
@@ -839,6 +847,7 @@ __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
     const long long off = zt.off;
     const cx<T> *tw = twp<T>(g, 2);
     const ZWaveOf<T, L> kw(c, zt.x, zt.y);
+    [[maybe_unused]] const long long TS = z_tab_row<L>(rs);
     // position of output register i of the forward transforms (recomputed at each use: a few
     // instructions from the thread index instead of registers held through the kernel)
     auto ee = [&](int i) {
@@ -1016,8 +1025,8 @@ __global__ __launch_bounds__(NTB) void k_z2c(Geo g_in, Z2Args a) {
                 int p, e;
                 const bool ok = F::template out_pos<-1>(i, p, e) && p < Pact;
                 const double *tab = g.tab64 + off + (ok ? z_tab<L>(e) * rs + p : 0);
-                w2 = ct::cld(tab + (long long)is * NC);
-                w3 = ct::cld(tab + (long long)(S + is) * NC);
+                w2 = ct::cld(tab + (long long)is * TS);
+                w3 = ct::cld(tab + (long long)(S + is) * TS);
             } else {
                 weight_w2_w3<T>(kmag[i], Ri, w2, w3);
             }

@@ -4,21 +4,20 @@
 
 namespace dft {
 
-// Spectral tables (FP64) of the z kernels, z <= n_z / 2 (z_tab): one thread per half-spectrum element.
+// Spectral tables (FP64) of the z kernels: one thread per element of a row.
 __global__ __launch_bounds__(256) void k_spec_tables(Geo g) {
-    const long long NC = g.NC;
+    const long long TS = spec_table_row(g.nx, g.ny, g.nz);
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= NC) return;
+    if (i >= TS) return;
     const Consts &c = *g.cs;
     const int Kx = g.Kx, S = g.S;
     const int kx = (int)(i % Kx);
     const long long t = i / Kx;
     const int y = (int)(t % g.ny), e = (int)(t / g.ny);
-    if (2 * e > g.nz) return;   // (even in k_z)
     const ZWave<double> kw(c, kx, y);
     const double kmag = kw.kmag(e);
     double *t64 = const_cast<double *>(g.tab64);
-    auto put = [&](int row, double v) { ct::gst(t64 + (long long)row * NC + i, v); };
+    auto put = [&](int row, double v) { ct::gst(t64 + (long long)row * TS + i, v); };
     for (int s = 0; s < S; ++s) {
         double w2, w3;
         weight_w2_w3<double>(kmag, c.R[s], w2, w3);
@@ -111,7 +110,7 @@ int spec_table_rows(int nz, int S, int es) {
 }
 
 void launch_spec_tables(const Geo &g, hipStream_t s) {
-    hipLaunchKernelGGL(k_spec_tables, dim3((unsigned)ct_cdiv(g.NC, 256)), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_spec_tables, dim3((unsigned)ct_cdiv(spec_table_row(g.nx, g.ny, g.nz), 256)), dim3(256), 0, s, g);
     ct_check("spectral tables");
 }
 

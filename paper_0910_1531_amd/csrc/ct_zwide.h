@@ -45,6 +45,7 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
     [[maybe_unused]] const Z1Const<T, (MS > 0 ? MS : 1)> kc(c);
     constexpr bool TAB = z_fp64_factors<T, L>();
     const double *tab = TAB ? g.tab64 + zt.off : nullptr;
+    [[maybe_unused]] const long long TS = z_tab_row<L>(rs);
     cx<T> v[F::V];
     if (wave < S) {
         const cx<T> *src = reinterpret_cast<const cx<T> *>(a.specA) + (long long)wave * NC + zt.off;
@@ -79,12 +80,12 @@ __global__ __launch_bounds__(kZWideThreads) void k_z1w(Geo g_in, Z1Args a) {
         if constexpr (MS == 0) {
 #pragma unroll
             for (int m = 0; m < 5; ++m) acc[m] = mk<T>(T(0), T(0));
-            for (int s = 0; s < S; ++s) z1_species<T>(c, kw, tab, NC, S, s, e, true, z_tab<L>(e) * rs + p, nv[s * F::TILE], acc);
+            for (int s = 0; s < S; ++s) z1_species<T>(c, kw, tab, TS, S, s, e, true, z_tab<L>(e) * rs + p, nv[s * F::TILE], acc);
         } else {
             cx<T> u[MS];
 #pragma unroll
             for (int s = 0; s < MS; ++s) u[s] = s < S ? nv[s * F::TILE] : mk<T>(T(0), T(0));
-            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, NC, S, es, e, true, z_tab<L>(e) * rs + p, u, acc,
+            z1_node<TAB>(kc, a.diff != 0, kw, pd, tab, TS, NC, S, es, e, true, z_tab<L>(e) * rs + p, u, acc,
                            reinterpret_cast<cx<T> *>(a.specA) + zt.off + ti);
         }
         if (n3) {
@@ -220,8 +221,8 @@ __global__ __launch_bounds__(kZWideThreads) void k_z2w(Geo g_in, Z2Args a) {
             T w2, w3;
             if constexpr (std::is_same<T, double>::value) {
                 const double *tab = g.tab64 + zt.off + z_tab<L>(e) * rs + p;
-                w2 = ct::cld(tab + (long long)is * NC);
-                w3 = ct::cld(tab + (long long)(S + is) * NC);
+                w2 = ct::cld(tab + (long long)is * z_tab_row<L>(rs));
+                w3 = ct::cld(tab + (long long)(S + is) * z_tab_row<L>(rs));
             } else {
                 weight_w2_w3<T>(kmag, Ri, w2, w3);
             }
