@@ -179,6 +179,9 @@ def _kernel_sources_sha256():
     return h.hexdigest()
 
 
+TUNED_LENGTHS = (16, 24, 32, 48, 64, 96, 128, 192, 256, 384)
+
+
 def _fit_threads(L, P, per, cap):
     t = 64
     while 2 * t <= cap and 2 * t * per <= L * P:
@@ -195,9 +198,10 @@ def pass_kernel(pass_name, fp32, n, schedule, S):
     if pass_name == "x_el":
         return f"dft::k_x3c<{T}, {n}>"
     if pass_name == "x_fmt":
-        if n < 64 or n > 384:   # one wave per field
-            return f"dft::k_x2w<{T}, {n}, {1 if fp32 else 0}>"
-        return f"dft::k_x2h<{T}, {n}, {1 if fp32 else 0}>"
+        form = 1 if fp32 and n in TUNED_LENGTHS else 0   # FP32 differences, else FP64 dPhi/dn
+        if n < 64 or (n > 384 and not fp32):   # one wave per field
+            return f"dft::k_x2w<{T}, {n}, {form}>"
+        return f"dft::k_x2h<{T}, {n}, {form}>"
     widths = {0: 8, 1: 4, 2: 16} if fp32 else {0: 4, 1: 2, 2: 8}
     if n not in (96, 128, 192, 256, 384):
         return None   # one shape (and small grids: one wave per transform)

@@ -110,7 +110,10 @@ constexpr int z_one_threads(int P) {
 // 96 28 / 46, 256^3 790 / 823; FP32 Z1 432 107 / 48, 324 67 / 58, 256 38 / 41; Z2 432 133 / 53,
 // 512 69 / 54, 324 58 / 80.  On cubes, two and three species: FP64 Z1 96^3 45 / 37.5, 52 / 43.7, 128^3
 // 65 / 59, 88 / 74; FP32 Z1 (with the waves of z1_waves) 128^3 47 / 41.7, 59 / 47.4, 192^3 108 / 100.6,
-// 143 / 114.5, but 96^3 31.7 / 35.3 and 256^3 338 / 352.
+// 143 / 114.5, but 96^3 31.7 / 35.3 and 256^3 338 / 352.  Held is the better at the other lengths of one shape: FP64 72^3
+// 29 / 33, 81^3 38 / 41, 108^3 77 / 78, 96 x 96 x 216 119 / 140, 72 x 72 x 243 93 / 107; FP32 (pair factors from the
+// tables) 72^3 23.6 / 27.6, 96 x 96 x 216 85 / 98, 64 x 64 x 162 38 / 46, and at 108 and 144 by the size of the grid:
+// 64 x 64 x 144 35 / 41 but 144^3 113 / 100.
 template <typename T, int L>
 constexpr bool z1_redo() {
     if (sizeof(T) == 8) return L == 96 || L == 128 || L == 144 || L == 162 || L == 192 || L == 256 || L == 384 || L == 432 || L == 486;

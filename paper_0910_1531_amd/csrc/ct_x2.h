@@ -249,9 +249,10 @@ __device__ __forceinline__ void x2h_swap_and_nodes(const X2Args &a, long long N,
 }
 
 // Waves per SIMD that the registers allow without (or with few) spills, by the values a field has per
-// lane (four, six or eight) and the nodewise form: FP32 differences 126 registers; FP64 about 200, or
-// 168 with 6 spilled at the lengths whose lanes are partly idle.  Measured in FP64: 96^3 63 us at two
-// waves, 55 at three; 256^3 699 at two, 816 at three.
+// lane (four, six or eight) and the nodewise form: FP32 differences 126 registers; FP64 about 200 at two waves.
+// In FP64 three waves (168 registers) spill little enough at 96 and 192 only; us, two waves / three: 96^3 63 / 55,
+// but 24 x 128 x 128 29.7 / 31.5, 36 x 96 x 96 31.7 / 34.4, 48 x 96 x 96 31.2 / 32.2, 72^3 32 / 44, 108^3 91 / 141,
+// 216 x 96 x 96 131 / 288, 256^3 699 / 816; 54 x 81 x 81 35.5 / 34.5 and 144^3 204 / 166 would gain.
 template <typename T, int L, int NODE>
 struct XHalf {
     static constexpr int NV = XRow<L>::template F<T>::template nout<1>();

@@ -505,7 +505,10 @@ dft_status dft_setup(const dft_params *params, const double *beta_vext, const do
             launch_spec_tables(g, c->stream);
         }
         // compact vector layout when every pass of the evaluation runs a compiled-length kernel and
-        // the rows are not the shortest (8 to 18 nodes but for 16)
+        // the rows are not the shortest (8 to 18 nodes but for 16), where its double y transforms cost more than
+        // the three spectra it saves (evaluation, us, ten spectra / compact, FP64: 12 x 32 x 32 82 / 108,
+        // 12 x 128 x 128 134 / 138, 9 x 96 x 96 104 / 115, 18 x 96 x 96 131 / 137, 8 x 96 x 96 103 / 102; FP32-mixed
+        // 12 x 128 x 128 118 / 127, 8 x 96 x 96 96 / 102)
         const bool short_rows = g.nx < 24 && g.nx != 16;
         g.compact = (g.tab64 && x2_ct_min_pairs(g.nx) > 0 && !short_rows && y_ct_variants(g.ny, false) > 0 &&
                      z_ct_variants(g.nz) > 0 && !(g.es && g.cut_lambda)) ? 1 : 0;
