@@ -311,7 +311,7 @@ __device__ __forceinline__ int z_tab(int e) {
 // Elements of a row of the tables (rs = n_y Kx, a z plane).
 template <int L>
 __device__ __forceinline__ long long z_tab_row(long long rs) {
-    return (L / 2 + 1) * rs;
+    return spec_table_row(L / 2 + 1, rs);
 }
 
 // Wavenumbers of the elements of one z pencil: column (x, y), z index e.  Only the indices are

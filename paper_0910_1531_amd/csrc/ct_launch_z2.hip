@@ -6,9 +6,9 @@ namespace dft {
 
 // Spectral tables (FP64) of the z kernels: one thread per element of a row.
 __global__ __launch_bounds__(256) void k_spec_tables(Geo g) {
-    const long long TS = spec_table_row(g.nx, g.ny, g.nz);
+    const long long rs = (long long)g.ny * g.Kx, used = (g.nz / 2 + 1) * rs, TS = spec_table_row(g.nz / 2 + 1, rs);
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= TS) return;
+    if (i >= used) return;
     const Consts &c = *g.cs;
     const int Kx = g.Kx, S = g.S;
     const int kx = (int)(i % Kx);
@@ -110,7 +110,7 @@ int spec_table_rows(int nz, int S, int es) {
 }
 
 void launch_spec_tables(const Geo &g, hipStream_t s) {
-    hipLaunchKernelGGL(k_spec_tables, dim3((unsigned)ct_cdiv(spec_table_row(g.nx, g.ny, g.nz), 256)), dim3(256), 0, s, g);
+    hipLaunchKernelGGL(k_spec_tables, dim3((unsigned)ct_cdiv((long long)(g.nz / 2 + 1) * g.ny * g.Kx, 256)), dim3(256), 0, s, g);
     ct_check("spectral tables");
 }
 

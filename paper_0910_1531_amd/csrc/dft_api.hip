@@ -99,7 +99,7 @@ Layout make_layout(const dft_params *p) {
         L.rho_ref = L.lp = L.nref = 0;
     }
     L.ntab = spec_table_rows(p->n[2], S, p->electrostatics ? 1 : 0);
-    L.tab64 = L.ntab ? take(sizeof(double) * (size_t)spec_table_row(p->n[0], p->n[1], p->n[2]) * L.ntab) : 0;
+    L.tab64 = L.ntab ? take(sizeof(double) * (size_t)spec_table_row(p->n[2] / 2 + 1, (long long)p->n[1] * (p->n[0] / 2 + 1)) * L.ntab) : 0;
     L.total = off;
     return L;
 }

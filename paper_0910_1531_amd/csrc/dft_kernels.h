@@ -61,7 +61,7 @@ struct Geo {
     int nprob = 1;
     long long pstride = 0;
     // FP64 spectral tables of the compiled-length z kernels, [row][z <= nz / 2][y][kx] (null: none; even
-    // in k_z, spec_table_row elements a row):
+    // in k_z; a row takes spec_table_row elements):
     // rows 0..S-1 w2_s(k), S..2S-1 w3_s(k), then with electrostatics the
     // screening-minus-Coulomb kernel K_ij(k) of each pair i <= j.
     const double *tab64 = nullptr;
@@ -207,9 +207,8 @@ int z_ct_variants(int L);              // launch shapes of the z kernels of leng
 int z1_ct_variants(int L);             // launch shapes of the Z1 pass (fused and split)
 // Rows of the spectral tables for S species (0 when the compiled z kernels cannot run).
 int spec_table_rows(int nz, int S, int es);
-__host__ __device__ inline long long spec_table_row(int nx, int ny, int nz) {
-    return (long long)(nz / 2 + 1) * ny * (nx / 2 + 1);
-}
+// Elements of a row for n z planes of rs elements: whole 4 KB (Z1 at 256^3, FP64: rows end to end 733 us, here 711).
+__host__ __device__ inline long long spec_table_row(long long n, long long rs) { return (n * rs + 511) / 512 * 512; }
 // Fill g.tab64 from the constants and twiddle tables.
 void launch_spec_tables(const Geo &g, hipStream_t s);
 template <typename T> void launch_z1(const Geo &g, const Z1Args &a, hipStream_t s);

@@ -1,4 +1,4 @@
-"""Workspace of the spectral tables: rows are even in k_z and hold z <= n_z / 2 only (host-only check)."""
+"""Workspace of the spectral tables: rows are even in k_z and hold z <= n_z / 2 only, in whole 4 KB (host-only check)."""
 import ctypes
 
 import pytest
@@ -19,6 +19,6 @@ def test_rows_hold_half_of_the_planes(n):
     prob = W.charged_sphere(n=n, h=0.1, sigma=(0.3, 0.24), conc=(0.5, 0.5), sphere_radius=0.3)
     es, hs = _params(prob), _params(prob)
     hs.electrostatics = 0
-    row = 8 * (n[2] // 2 + 1) * n[1] * (n[0] // 2 + 1)
+    row = 4096 * -(-8 * (n[2] // 2 + 1) * n[1] * (n[0] // 2 + 1) // 4096)
     # two species: the three pair rows come with electrostatics (buffers are aligned to 256 bytes)
     assert abs(_size(es) - _size(hs) - 3 * row) <= 256
